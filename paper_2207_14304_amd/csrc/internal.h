@@ -136,6 +136,9 @@ int launch_fit(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec,
                const float *ref, const float *ref_var, const uint8_t *ref_mask,
                const float *sci, const float *sci_var, const uint8_t *sci_mask,
                double *coeffs, int64_t *n_fit, int32_t *status);
+// coefficients, fit-set sizes and statuses from n_solves moment sums
+int launch_solve(argus_ctx *ctx, const argus_kernel_spec *spec, const double *sums, int stride,
+                 int n_solves, double *coeffs, int64_t *n_fit, int32_t *status);
 int launch_expand(argus_ctx *ctx, const argus_kernel_spec *spec, const double *coeffs,
                   float *stamps, float *bg);
 // chi2[s] = NaN where status[s] != ARGUS_OK (n solves)

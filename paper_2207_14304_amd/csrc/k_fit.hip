@@ -1,6 +1,6 @@
 // Kernel fit: basis tables, fused basis convolution + normal-equation
-// accumulation on MFMA, FP64 reduction of the partial sums, and the
-// Jacobi-scaled FP64 Cholesky solve.
+// accumulation on MFMA and FP64 reduction of the partial sums (the solve is
+// in k_solve.hip).
 //
 // Model (Alard & Lupton 1998; Alard 2000): the design row of pixel p is
 //   X_p = [P_m(p) C_k(p)]_{k<nb, m<nP} ++ [P_m(p)]_{m<nPbg},
@@ -18,7 +18,6 @@ using argus_fit::FitArgs;
 using argus_fit::FitShape;
 using argus_fit::SW;
 using argus_fit::NTHR;
-using argus_fit::qidx;
 
 namespace {
 
@@ -119,228 +118,6 @@ __global__ void sum_parts_kernel(const double *in, int stride, int n_in, int gro
     out[(size_t)set * stride + e] = s;
 }
 
-// ---------------------------------------------------------------------------
-// Solve: assemble A and b from the moments, Jacobi scale, right-looking
-// Cholesky on the packed lower triangle, two triangular solves.
-struct SolveArgs {
-    const double *sums;        // [n_solves][stride]
-    int stride;
-    int nb, D, Dbg, n;
-    double *coeffs;
-    int64_t *n_fit;
-    int32_t *status;
-    double *gtri;              // global fallback storage for the factor (or null)
-};
-
-__device__ __forceinline__ void unpack_row(int r, int nb, int D, int Dbg, int &k, int &p, int &q) {
-    int nP = (D + 1) * (D + 2) / 2;
-    int m;
-    int Dm;
-    if (r < nb * nP) { k = r / nP; m = r % nP; Dm = D; }
-    else { k = nb; m = r - nb * nP; Dm = Dbg; }
-    // monomial m of degree <= Dm: p outer, q inner
-    int pp = 0;
-    while (m > Dm - pp) { m -= Dm - pp + 1; ++pp; }
-    p = pp;
-    q = m;
-}
-
-__device__ __forceinline__ double gram_at(const double *G, int q, int k, int l) {
-    // G[q][bp][16][16], blocks (0,0), (0,1), (1,1) of the symmetric 32x32 moment
-    if (k > l) { int t = k; k = l; l = t; }
-    const double *g = G + (size_t)q * 768;
-    if (l < 16) return g[k * 16 + l];
-    if (k < 16) return g[256 + k * 16 + (l - 16)];
-    return g[512 + (k - 16) * 16 + (l - 16)];
-}
-
-__device__ double block_sum(double v, double *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += red[i];
-    return s;
-}
-
-constexpr int SOLVE_THREADS = 1024;
-
-// One workgroup of SOLVE_THREADS per solve.  Rows of the packed triangle are
-// addressed through a table of row offsets; a wave walks a row with its
-// lanes on consecutive columns (contiguous in the packed storage).  The
-// factorisation takes one barrier per two columns: a phase applies the
-// unscaled columns j and j + 1 to the trailing matrix in one pass and scales
-// the previous phase's two columns, which no thread reads during the phase.
-// GLT: the factor lives in global memory (a.gtri, for devices whose LDS is too
-// small); otherwise it is in LDS and every access is a plain LDS instruction.
-template <bool GLT>
-__global__ __launch_bounds__(SOLVE_THREADS) void fit_solve_kernel(SolveArgs a) {
-    constexpr int NT = SOLVE_THREADS, NWV = NT / 64;
-    extern __shared__ double sl[];
-    __shared__ int roff[256];             // r (r + 1) / 2 for r < n <= 192
-    __shared__ short rk[256];             // basis, x-power and y-power of row r
-    __shared__ unsigned char rp[256], rq[256];
-    __shared__ double rdiag[256];         // 1 / L_ii
-    __shared__ double tcol[2][256];       // column j + 1 after column j, by phase parity
-    const int n = a.n, tid = threadIdx.x, sol = blockIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int ntri = n * (n + 1) / 2;
-    double *L = GLT ? a.gtri + (size_t)sol * ntri : sl;
-    double *bb = sl + (GLT ? 0 : ntri);
-    double *dd = bb + n;
-    double *red = dd + n;                 // [NWV]
-    __shared__ int bad;
-    const double *sums = a.sums + (size_t)sol * a.stride;
-    const int D = a.D, NQ = (2 * D + 1) * (2 * D + 2) / 2;
-    const double cnt = sums[(size_t)NQ * 768 + (D + 1) * (D + 2) / 2 * 32];
-    double *co = a.coeffs + (size_t)sol * n;
-    if (tid == 0) {
-        bad = 0;
-        if (a.n_fit) a.n_fit[sol] = (int64_t)cnt;
-    }
-    if (cnt < (double)n) {
-        for (int i = tid; i < n; i += NT) co[i] = __builtin_nan("");
-        if (tid == 0) a.status[sol] = ARGUS_ETOOFEW;
-        return;
-    }
-    for (int r = tid; r < n; r += NT) {
-        int k, p, q;
-        unpack_row(r, a.nb, D, a.Dbg, k, p, q);
-        roff[r] = r * (r + 1) / 2;
-        rk[r] = (short)k;
-        rp[r] = (unsigned char)p;
-        rq[r] = (unsigned char)q;
-    }
-    __syncthreads();
-    // assemble the packed lower triangle and the rhs
-    for (int r = wv; r < n; r += NWV) {
-        const int kr = rk[r], pr = rp[r], qr = rq[r];
-        for (int c = lane; c <= r; c += 64)
-            L[roff[r] + c] = gram_at(sums, qidx(pr + rp[c], qr + rq[c], 2 * D), kr, rk[c]);
-    }
-    for (int r = tid; r < n; r += NT) bb[r] = sums[(size_t)NQ * 768 + qidx(rp[r], rq[r], D) * 32 + rk[r]];
-    __syncthreads();
-    for (int r = tid; r < n; r += NT) {
-        double dg = L[roff[r] + r];
-        if (!(dg > 0.0)) bad = 1;
-        dd[r] = dg > 0.0 ? 1.0 / sqrt(dg) : 0.0;
-    }
-    __syncthreads();
-    if (bad) {
-        for (int i = tid; i < n; i += NT) co[i] = __builtin_nan("");
-        if (tid == 0) a.status[sol] = ARGUS_ESINGULAR;
-        return;
-    }
-    // Jacobi scaling
-    for (int r = wv; r < n; r += NWV) {
-        const double dr = dd[r];
-        for (int c = lane; c <= r; c += 64) L[roff[r] + c] *= dr * dd[c];
-    }
-    for (int r = tid; r < n; r += NT) bb[r] *= dd[r];
-    __syncthreads();
-    double mx = 0.0;
-    for (int r = tid; r < n; r += NT) mx = fmax(mx, L[roff[r] + r]);
-    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if (lane == 0) red[wv] = mx;
-    __syncthreads();
-    double maxdiag = 0.0;
-    for (int i = 0; i < NWV; ++i) maxdiag = fmax(maxdiag, red[i]);
-    const double tol = (double)n * 0x1p-52 * maxdiag;
-    __syncthreads();
-    // Right-looking Cholesky, two columns per barrier.  A phase takes columns
-    // j and j + 1 as they stand (updated by every earlier column) and applies
-    // both to the trailing rows and columns c >= j + 2 in one pass:
-    //   t_i = a_i,j+1 - a_ij a_j+1,j / a_jj          (column j + 1 after column j)
-    //   p1  = a_j+1,j+1 - a_j+1,j^2 / a_jj           (its pivot)
-    //   a_ic -= a_ij a_cj / a_jj + t_i t_c / p1      (c <= i)
-    // Every thread forms p1 itself and t_c on the fly from the two columns,
-    // which nobody writes during the phase (t_i goes to tcol), so the phase
-    // needs no barrier inside.  tcol alternates between two buffers: a phase
-    // writes one while the scaling at its start still reads the other.  The columns are scaled to L at the start of
-    // the next phase: L_ij = a_ij / sqrt(a_jj), L_i,j+1 = t_i / sqrt(p1); the
-    // diagonals stay as they are and the substitutions use rdiag = 1 / L_jj.
-    double pv0 = 0.0, pv1 = 0.0;         // pivots of the previous phase
-    for (int j = 0;; j += 2) {
-        if (j > 0) {
-            const int c0 = j - 2;
-            const double rs0 = 1.0 / sqrt(pv0), rs1 = 1.0 / sqrt(pv1);
-            for (int i = c0 + 1 + tid; i < n; i += NT) L[roff[i] + c0] *= rs0;
-            const double *tp = tcol[((j >> 1) - 1) & 1];
-            for (int i = c0 + 2 + tid; i < n; i += NT) L[roff[i] + c0 + 1] = tp[i] * rs1;
-            if (tid == 0) {
-                rdiag[c0] = rs0;
-                rdiag[c0 + 1] = rs1;
-            }
-        }
-        if (j >= n) break;
-        const double piv = L[roff[j] + j];
-        if (!(piv > tol)) {
-            if (tid == 0) bad = 1;
-            break;
-        }
-        if (j == n - 1) {                  // odd count: the last column alone
-            if (tid == 0) rdiag[j] = 1.0 / sqrt(piv);
-            break;
-        }
-        const double ip = 1.0 / piv;
-        const double r = L[roff[j + 1] + j] * ip;
-        const double p1 = L[roff[j + 1] + j + 1] - L[roff[j + 1] + j] * r;
-        if (!(p1 > tol)) {
-            if (tid == 0) bad = 1;
-            break;
-        }
-        const double ip1 = 1.0 / p1;
-        // rows i >= j + 2, a wave per row, its lanes on consecutive columns
-        double *tw = tcol[(j >> 1) & 1];
-        for (int i = j + 2 + wv; i < n; i += NWV) {
-            double *Li = L + roff[i];
-            const double lij = Li[j];
-            const double ti = Li[j + 1] - lij * r;
-            if (lane == 0) tw[i] = ti;
-            const double a0 = lij * ip, a1 = ti * ip1;
-            for (int c = j + 2 + lane; c <= i; c += 64) {
-                const double lcj = L[roff[c] + j];
-                const double tc = L[roff[c] + j + 1] - lcj * r;
-                Li[c] -= a0 * lcj + a1 * tc;
-            }
-        }
-        pv0 = piv;
-        pv1 = p1;
-        __syncthreads();
-    }
-    __syncthreads();
-    if (bad) {
-        for (int i = tid; i < n; i += NT) co[i] = __builtin_nan("");
-        if (tid == 0) a.status[sol] = ARGUS_ESINGULAR;
-        return;
-    }
-    // forward and back substitution (wave 0)
-    if (tid < 64) {
-        for (int i = 0; i < n; ++i) {
-            double s = 0.0;
-            for (int k = tid; k < i; k += 64) s += L[roff[i] + k] * bb[k];
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-            double v = (bb[i] - s) * rdiag[i];
-            __builtin_amdgcn_wave_barrier();
-            bb[i] = v;      // every lane stores the same value, so each lane sees it
-            __builtin_amdgcn_wave_barrier();
-        }
-        for (int i = n - 1; i >= 0; --i) {
-            double s = 0.0;
-            for (int k = i + 1 + tid; k < n; k += 64) s += L[roff[k] + i] * bb[k];
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-            double v = (bb[i] - s) * rdiag[i];
-            __builtin_amdgcn_wave_barrier();
-            bb[i] = v;
-            __builtin_amdgcn_wave_barrier();
-        }
-        for (int i = tid; i < n; i += 64) co[i] = dd[i] * bb[i];
-        if (tid == 0) a.status[sol] = ARGUS_OK;
-    }
-}
-
 // K_m = sum_k a_{k nP + m} B_k (FP64), bg_m = a_{nb nP + m}
 __global__ void expand_kernel(const BasisTables *T, const double *coeffs, int n, int nP, int nPb,
                               float *stamps, float *bg) {
@@ -364,9 +141,7 @@ int fit_launch_d(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, Fi
     const int n_parts = n_regions * parts_per_region;
     const int group = 64;
     const int n_g1 = spec->mode == ARGUS_FIT_GLOBAL ? (n_parts + group - 1) / group : 0;
-    const int n = fa.nb * argus_npoly(D) + argus_npoly(spec->bg_degree);
-    size_t need = ((size_t)n_parts + n_g1 + n_regions) * fa.stride * sizeof(double) +
-                  (size_t)n * (n + 1) / 2 * sizeof(double) * n_regions;
+    size_t need = ((size_t)n_parts + n_g1 + n_regions) * fa.stride * sizeof(double);
     int rc = argus_ws_reserve(ctx, need + 256);
     if (rc) return rc;
     double *base = (double *)ctx->ws;
@@ -520,42 +295,7 @@ int launch_fit(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, cons
         default: rc = fit_launch_d<2>(ctx, d, spec, fa, n_regions, parts_per_region, &sums); break;
     }
     if (rc) return rc;
-    SolveArgs sa;
-    sa.sums = sums;
-    sa.stride = fa.stride;
-    sa.nb = fa.nb;
-    sa.D = spec->spatial_degree;
-    sa.Dbg = spec->bg_degree;
-    sa.n = fa.nb * argus_npoly(sa.D) + argus_npoly(sa.Dbg);
-    sa.coeffs = coeffs;
-    sa.n_fit = n_fit;
-    sa.status = status;
-    sa.gtri = nullptr;
-    size_t lds = ((size_t)sa.n * (sa.n + 1) / 2 + 2 * sa.n + SOLVE_THREADS / 64) * sizeof(double);
-    int dev_max = 0;
-    ARGUS_HIP_CHECK(ctx, hipDeviceGetAttribute(&dev_max, hipDeviceAttributeMaxSharedMemoryPerBlock,
-                                               ctx->device));
-    hipFuncAttributes fattr;
-    ARGUS_HIP_CHECK(ctx, hipFuncGetAttributes(&fattr, (const void *)fit_solve_kernel<false>));
-    if (lds + fattr.sharedSizeBytes > (size_t)dev_max) {
-        // factor in global memory (after the sums in the workspace)
-        size_t tri = (size_t)sa.n * (sa.n + 1) / 2 * sizeof(double) * n_regions;
-        size_t used = (size_t)((char *)(sums + (size_t)n_regions * fa.stride) - (char *)ctx->ws);
-        if (used + tri > ctx->ws_bytes)
-            return argus_fail(ctx, ARGUS_ENOMEM, "solve storage does not fit the workspace");
-        sa.gtri = sums + (size_t)n_regions * fa.stride;
-        lds = ((size_t)2 * sa.n + SOLVE_THREADS / 64) * sizeof(double);
-    }
-    const void *kfn = sa.gtri ? (const void *)fit_solve_kernel<true> : (const void *)fit_solve_kernel<false>;
-    ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    argus_time_begin(ctx);
-    if (sa.gtri)
-        hipLaunchKernelGGL(fit_solve_kernel<true>, dim3(n_regions), dim3(SOLVE_THREADS), lds, ctx->stream, sa);
-    else
-        hipLaunchKernelGGL(fit_solve_kernel<false>, dim3(n_regions), dim3(SOLVE_THREADS), lds, ctx->stream, sa);
-    ARGUS_HIP_CHECK(ctx, hipGetLastError());
-    argus_time_end(ctx, "fit_solve");
-    return ARGUS_OK;
+    return launch_solve(ctx, spec, sums, fa.stride, n_regions, coeffs, n_fit, status);
 }
 
 namespace {
