@@ -404,7 +404,7 @@ int argus_resample_healpix(argus_ctx *ctx, argus_dims dims, const float *cal, co
  * of the tile border | FOOT within 2r (Chebyshev) of a masked or off-frame
  * pixel, with D = snr = flux = 0 where flagged.  sum P_D^2 is written to
  * pd2 (DEVICE f64, nullable).  FP64 transforms and arithmetic; workspace
- * grows to about 70 n L^2 bytes.  Errors: ARGUS_EINVAL (null pointers,
+ * grows to about 17 n L^2 bytes.  Errors: ARGUS_EINVAL (null pointers,
  * scalars), ARGUS_ESHAPE (L, r, n). */
 int argus_zogy(argus_ctx *ctx, argus_dims dims, const float *new_img, const uint8_t *new_mask,
                const float *ref, const uint8_t *ref_mask, const int32_t *origins, int n_tiles,
