@@ -845,7 +845,7 @@ __global__ void cnn_pack_kernel(PackArgs pa) {
 }
 
 // ---------------------------------------------------------------------------
-// Stamp extraction: one workgroup of NTS threads per tile.  Candidates are positive
+// Stamp extraction.  Candidates are positive
 // reference local maxima (strictly above earlier 8-neighbours in raster
 // order, >= later ones) whose stamp lies inside the frame and whose peak
 // stands snr_min noise sigmas above the tile's sky (the median of its
@@ -860,8 +860,18 @@ __global__ void cnn_pack_kernel(PackArgs pa) {
 // float bit patterns (positive floats order like their bits; 4096 buckets
 // of 1/8 octave) picks the lowest bucket whose suffix count fits, so every
 // retained candidate is brighter than every dropped one.
+//
+// A frame has few tiles (16 of 256 x 256 pixels in the surrogate's use), so
+// the passes over the tiles' pixels -- three radix-select histograms for the
+// sky, the candidate test -- run on many workgroups per tile (stamp_hist_kernel,
+// stamp_cand_kernel) and only the ranking, the walk and the stamps on one
+// (stamps_kernel).  Their histograms and candidate lists live in the tile's
+// part of the output X, which the last kernel overwrites; where that is too
+// small for them (few or small stamps per tile) one workgroup per tile does
+// every pass itself.  1024^2 frame, 4 x 4 tiles: 627 -> 90 us.
 constexpr int NTS = 1024;      // threads of the stamp extraction workgroup
-constexpr int WW = 8;          // its waves that walk the ranking (LDS stamp slots)
+constexpr int WW = NTS / 64;   // waves that walk the ranking
+constexpr int PXL = 16;        // stamp pixels a lane holds (31 x 31 / 64, rounded up)
 constexpr int MAXC = 2048;
 constexpr int NBUCKET = 4096;
 // inputs near unit size: a unit-sum 31x31 stamp has values of order 1e-3,
@@ -879,22 +889,50 @@ struct StampArgs {
     float snr_min;
 };
 
-// Border median of an n x n stamp (4(n-1) values) by a wave-wide bitonic
-// sort in a 256-slot LDS buffer; the middle pair is averaged in FP32.
-__device__ __forceinline__ float border_median_wave(const float *st, int n, float *buf, int lane) {
+// Border median of the n x n stamp at st (4(n-1) <= 120 values), two values a
+// lane: the middle pair, averaged in FP32, are the values with at most k
+// smaller and more than k not larger ones, counted against every value by
+// readlane broadcasts (a wave-wide bitonic sort of the values in LDS takes 36
+// dependent steps, about twice the time).  With a NaN among them the sort
+// decides.
+__device__ __forceinline__ float border_median_wave(const float *st, int64_t pitch, int n,
+                                                    float *buf, int lane) {
     const int nb = 4 * (n - 1);
-    for (int i = lane; i < 256; i += 64) {
-        float v = __builtin_inff();
+    float bv[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = lane + 64 * h;
+        bv[h] = __builtin_inff();
         if (i < nb) {
             int y, x;
             if (i < n) { y = 0; x = i; }
             else if (i < 2 * n) { y = n - 1; x = i - n; }
             else if (i < 2 * n + n - 2) { y = 1 + (i - 2 * n); x = 0; }
             else { y = 1 + (i - 3 * n + 2); x = n - 1; }
-            v = st[y * n + x];
+            bv[h] = st[y * pitch + x];
         }
-        buf[i] = v;
     }
+    if (!__any(bv[0] != bv[0] || bv[1] != bv[1])) {
+        int less[2] = {0, 0}, leq[2] = {0, 0};
+        for (int i = 0; i < nb; ++i) {
+            const float b = __uint_as_float(__builtin_amdgcn_readlane(
+                __float_as_uint(i < 64 ? bv[0] : bv[1]), i & 63));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                less[h] += b < bv[h] ? 1 : 0;
+                leq[h] += b <= bv[h] ? 1 : 0;
+            }
+        }
+        auto rank = [&](int k) {
+            const uint64_t m0 = __ballot(less[0] <= k && k < leq[0]);
+            const uint64_t m1 = __ballot(less[1] <= k && k < leq[1]);
+            return __uint_as_float(__builtin_amdgcn_readlane(
+                __float_as_uint(m0 ? bv[0] : bv[1]), __builtin_ctzll(m0 ? m0 : m1)));
+        };
+        // (nb is a multiple of 4)
+        return (rank(nb / 2 - 1) + rank(nb / 2)) * 0.5f;
+    }
+    for (int h = 0; h < 4; ++h) buf[lane + 64 * h] = h < 2 ? bv[h] : __builtin_inff();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (int k = 2; k <= 256; k <<= 1) {
@@ -959,7 +997,190 @@ __device__ uint32_t tile_select(const StampArgs &a, int x0, int y0, int tw, int 
     return prefix;
 }
 
-__global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a) {
+// Scratch of a tile in its part of X (32-bit words): candidate count, sky,
+// the digit histograms of the radix select (11, 11 and 10 bits; the two middle
+// ranks may part ways, so the later passes have one each), candidate list
+// (value bits, raster index).
+constexpr int SC_NCAND = 0, SC_SKY = 1, SC_H1 = 64, SC_H2 = SC_H1 + 2048, SC_H3 = SC_H2 + 4096,
+              SC_LIST = SC_H3 + 2048;
+constexpr int SC_MIN = SC_LIST + 2 * MAXC;
+constexpr int SCH = 256;       // threads of a scan workgroup
+constexpr int SC_PX = 2048;    // pixels of a scan workgroup, about (16 tiles of 256^2: 512 workgroups)
+
+struct TileRect {
+    int x0, y0, tw, th;
+    __device__ TileRect(const StampArgs &a, int t) {
+        const int tx = t % a.TX, ty = t / a.TX;
+        x0 = (int)((int64_t)tx * a.W / a.TX);
+        y0 = (int)((int64_t)ty * a.H / a.TY);
+        tw = (int)((int64_t)(tx + 1) * a.W / a.TX) - x0;
+        th = (int)((int64_t)(ty + 1) * a.H / a.TY) - y0;
+    }
+};
+
+__device__ __forceinline__ uint32_t *tile_scratch(const StampArgs &a, int t) {
+    return (uint32_t *)a.X + (size_t)t * a.S * (2 * a.r + 1) * (2 * a.r + 1);
+}
+
+// candidate test; the stamp-in-frame bound keeps every neighbour in the frame
+__device__ __forceinline__ bool stamp_cand(const StampArgs &a, int y, int x, float sky, float &c) {
+    const int64_t P = a.pitch;
+    if (y < a.r || x < a.r || y >= a.H - a.r || x >= a.W - a.r) return false;
+    const int64_t o = (int64_t)y * P + x;
+    const float *q = a.ref + o;
+    c = q[0];
+    if (!(c > 0.f)) return false;
+    if (!(c > q[-P - 1] && c > q[-P] && c > q[-P + 1] && c > q[-1] && c >= q[1] &&
+          c >= q[P - 1] && c >= q[P] && c >= q[P + 1]))
+        return false;
+    const float vv = a.rvar[o];
+    return vv > 0.f && (c - sky) / sqrtf(vv) >= a.snr_min;
+}
+
+// Bin of the 0-based rank k in a histogram of nbins (a multiple of SCH) and
+// the rank within it; total is the histogram's sum (k >= total: the last bin).
+__device__ void find_digit(const uint32_t *hist, int nbins, uint32_t k, uint32_t &digit,
+                           uint32_t &rest, uint32_t &total) {
+    __shared__ uint32_t wsum[SCH / 64], out[2];
+    const int tid = threadIdx.x, lane = tid & 63, per = nbins / SCH;
+    uint32_t v[8], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        v[i] = i < per ? hist[tid * per + i] : 0;
+        sum += v[i];
+    }
+    uint32_t inc = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(inc, off);
+        if (lane >= off) inc += u;
+    }
+    if (tid == 0) out[0] = nbins - 1, out[1] = 0;
+    if (lane == 63) wsum[tid >> 6] = inc;
+    __syncthreads();
+    uint32_t base = inc - sum;
+    total = 0;
+    for (int w = 0; w < SCH / 64; ++w) {
+        if (w < (tid >> 6)) base += wsum[w];
+        total += wsum[w];
+    }
+    if (k >= base && k < base + sum) {
+        uint32_t b = base;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (i < per && k >= b && k < b + v[i]) out[0] = tid * per + i, out[1] = k - b;
+            b += v[i];
+        }
+    }
+    __syncthreads();
+    digit = out[0];
+    rest = out[1];
+    __syncthreads();
+}
+
+// Key prefixes of the two middle ranks after the passes before PASS (11 or 22
+// bits; PASS 4: the whole keys), and the number of unmasked pixels.
+template <int PASS>
+__device__ void find_prefixes(const uint32_t *sc, uint32_t &p1, uint32_t &p2, uint32_t &n) {
+    uint32_t d, k1, k2, tot;
+    p1 = p2 = 0;
+    find_digit(sc + SC_H1, 2048, 0, d, k1, n);
+    if (n == 0) return;
+    find_digit(sc + SC_H1, 2048, (n - 1) / 2, p1, k1, tot);
+    find_digit(sc + SC_H1, 2048, n / 2, p2, k2, tot);
+    if constexpr (PASS >= 3) {
+        const bool one = p1 == p2;
+        find_digit(sc + SC_H2, 2048, k1, d, k1, tot);
+        p1 = p1 << 11 | d;
+        find_digit(sc + SC_H2 + (one ? 0 : 2048), 2048, k2, d, k2, tot);
+        p2 = p2 << 11 | d;
+    }
+    if constexpr (PASS >= 4) {
+        const bool one = p1 == p2;
+        find_digit(sc + SC_H3, 1024, k1, d, k1, tot);
+        p1 = p1 << 10 | d;
+        find_digit(sc + SC_H3 + (one ? 0 : 1024), 1024, k2, d, k2, tot);
+        p2 = p2 << 10 | d;
+    }
+}
+
+// clears the histograms and the candidate count of every tile
+__global__ __launch_bounds__(SCH) void stamp_clear_kernel(StampArgs a) {
+    uint32_t *sc = tile_scratch(a, blockIdx.x);
+    for (int i = threadIdx.x; i < SC_LIST; i += SCH) sc[i] = 0;
+}
+
+// Digit PASS (1..3) of the unmasked reference keys in a tile's rows
+// [blockIdx.y rows, ...), counted for each middle rank's prefix.
+template <int PASS>
+__global__ __launch_bounds__(SCH) void stamp_hist_kernel(StampArgs a, int rows) {
+    constexpr int NB = PASS == 3 ? 1024 : 2048, SHIFT = PASS == 1 ? 21 : PASS == 2 ? 10 : 0;
+    __shared__ uint32_t h[PASS == 1 ? NB : 2 * NB];
+    constexpr int NH = sizeof(h) / sizeof(h[0]);
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const TileRect q(a, t);
+    uint32_t *sc = tile_scratch(a, t);
+    const int ya = min((int)blockIdx.y * rows, q.th), npix = (min(ya + rows, q.th) - ya) * q.tw;
+    if (npix <= 0) return;
+    for (int i = tid; i < NH; i += SCH) h[i] = 0;
+    uint32_t p1 = 0, p2 = 0, n = 0;
+    if constexpr (PASS > 1) {
+        find_prefixes<PASS>(sc, p1, p2, n);
+        if (n == 0) return;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < npix; i += SCH) {
+        const int64_t o = (int64_t)(q.y0 + ya + i / q.tw) * a.pitch + q.x0 + i % q.tw;
+        const uint32_t key = fkey(a.ref[o]);
+        if (a.rmask[o] != 0) continue;
+        const uint32_t d = (key >> SHIFT) & (NB - 1);
+        if constexpr (PASS == 1) {
+            atomicAdd(&h[d], 1u);
+        } else {
+            const uint32_t pre = key >> (PASS == 2 ? 21 : 10);
+            if (pre == p1) atomicAdd(&h[d], 1u);
+            else if (pre == p2) atomicAdd(&h[NB + d], 1u);
+        }
+    }
+    __syncthreads();
+    uint32_t *out = sc + (PASS == 1 ? SC_H1 : PASS == 2 ? SC_H2 : SC_H3);
+    for (int i = tid; i < NH; i += SCH)
+        if (h[i]) atomicAdd(&out[i], h[i]);
+}
+
+// The tile's sky, and the candidates among its rows [blockIdx.y rows, ...).
+__global__ __launch_bounds__(SCH) void stamp_cand_kernel(StampArgs a, int rows, uint32_t cap) {
+    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const TileRect q(a, t);
+    uint32_t *sc = tile_scratch(a, t);
+    const int ya = min((int)blockIdx.y * rows, q.th), npix = (min(ya + rows, q.th) - ya) * q.tw;
+    uint32_t p1, p2, n;
+    find_prefixes<4>(sc, p1, p2, n);
+    float sky = __builtin_inff();
+    if (n > 0) sky = (n & 1) ? unkey(p1) : (unkey(p1) + unkey(p2)) * 0.5f;
+    if (blockIdx.y == 0 && tid == 0) sc[SC_SKY] = __float_as_uint(sky);
+    for (int i = tid; i - lane < npix; i += SCH) {
+        const int y = q.y0 + ya + i / q.tw, x = q.x0 + i % q.tw;
+        float c = 0.f;
+        const bool is = i < npix && stamp_cand(a, y, x, sky, c);
+        const uint64_t b = __ballot(is);
+        if (!b) continue;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&sc[SC_NCAND], (uint32_t)__popcll(b));
+        base = __shfl(base, 0);
+        const uint32_t slot = base + __popcll(b & ((1ull << lane) - 1));
+        if (is && slot < cap) {
+            sc[SC_LIST + 2 * slot] = __float_as_uint(c);
+            sc[SC_LIST + 2 * slot + 1] = (uint32_t)((int64_t)y * a.W + x);
+        }
+    }
+}
+
+// The ranking, the walk and the stamps of a tile.  LIST: sky and candidates
+// come from the scan kernels (a list that overflowed is taken from the pixels
+// again); else the workgroup finds them itself.
+template <bool LIST>
+__global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a, uint32_t cap) {
     __shared__ unsigned long long keys[MAXC];
     __shared__ int hist[NBUCKET];
     __shared__ int psum[NTS];
@@ -968,97 +1189,101 @@ __global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a) {
     __shared__ float fmed[WW];
     __shared__ int acc_y[64], acc_x[64];
     __shared__ float acc_m[64];
-    extern __shared__ __align__(16) float sst[];   // per walking wave: 2 stamps + 256 sort slots
+    __shared__ float sbuf[WW][256];                // sort slots of the median
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tx = t % a.TX, ty = t / a.TX;
-    const int x0 = (int)((int64_t)tx * a.W / a.TX), x1 = (int)((int64_t)(tx + 1) * a.W / a.TX);
-    const int y0 = (int)((int64_t)ty * a.H / a.TY), y1 = (int)((int64_t)(ty + 1) * a.H / a.TY);
+    const TileRect tile(a, t);
+    const int x0 = tile.x0, y0 = tile.y0, tw = tile.tw, npix = tile.tw * tile.th;
     const int r = a.r, n = 2 * r + 1, npx = n * n;
     const int64_t P = a.pitch;
-    const int tw = x1 - x0, npix = tw * (y1 - y0);
-    // the tile's sky: median of its unmasked reference pixels (middle pair
-    // averaged in FP32); +inf when every pixel is masked (no candidates)
-    __shared__ int s_nun;
-    if (tid == 0) s_nun = 0;
-    __syncthreads();
-    {
-        int cnt = 0;
-        for (int i = tid; i < npix; i += NTS)
-            cnt += a.rmask[(int64_t)(y0 + i / tw) * P + x0 + i % tw] == 0;
-        atomicAdd(&s_nun, cnt);
-    }
-    __syncthreads();
-    const int nun = s_nun;
     float sky = __builtin_inff();
-    if (nun > 0) {
-        const float v1 = unkey(tile_select(a, x0, y0, tw, npix, (nun - 1) / 2, hist));
-        if (nun & 1) {
-            sky = v1;
-        } else {
-            const float v2 = unkey(tile_select(a, x0, y0, tw, npix, nun / 2, hist));
-            sky = (v1 + v2) * 0.5f;
+    uint32_t nlist = 0;
+    const uint32_t *list = nullptr;
+    if constexpr (LIST) {
+        const uint32_t *sc = tile_scratch(a, t);
+        sky = __uint_as_float(sc[SC_SKY]);
+        nlist = sc[SC_NCAND];
+        list = sc + SC_LIST;
+    } else {
+        // the tile's sky: median of its unmasked reference pixels (middle pair
+        // averaged in FP32); +inf when every pixel is masked (no candidates)
+        __shared__ int s_nun;
+        if (tid == 0) s_nun = 0;
+        __syncthreads();
+        {
+            int cnt = 0;
+            for (int i = tid; i < npix; i += NTS)
+                cnt += a.rmask[(int64_t)(y0 + i / tw) * P + x0 + i % tw] == 0;
+            atomicAdd(&s_nun, cnt);
+        }
+        __syncthreads();
+        const int nun = s_nun;
+        if (nun > 0) {
+            const float v1 = unkey(tile_select(a, x0, y0, tw, npix, (nun - 1) / 2, hist));
+            if (nun & 1) {
+                sky = v1;
+            } else {
+                const float v2 = unkey(tile_select(a, x0, y0, tw, npix, nun / 2, hist));
+                sky = (v1 + v2) * 0.5f;
+            }
         }
     }
     for (int i = tid; i < NBUCKET; i += NTS) hist[i] = 0;
     if (tid == 0) { ncand = 0; nacc = 0; }
     __syncthreads();
-    // candidate test; the stamp-in-frame bound keeps every neighbour in the frame
-    auto is_cand = [&](int y, int x, float &c) -> bool {
-        if (y < r || x < r || y >= a.H - r || x >= a.W - r) return false;
-        const int64_t o = (int64_t)y * P + x;
-        const float *q = a.ref + o;
-        c = q[0];
-        if (!(c > 0.f)) return false;
-        if (!(c > q[-P - 1] && c > q[-P] && c > q[-P + 1] && c > q[-1] && c >= q[1] &&
-              c >= q[P - 1] && c >= q[P] && c >= q[P + 1]))
-            return false;
-        const float vv = a.rvar[o];
-        return vv > 0.f && (c - sky) / sqrtf(vv) >= a.snr_min;
-    };
-    for (int i = tid; i < npix; i += NTS) {
-        float c;
-        if (is_cand(y0 + i / tw, x0 + i % tw, c)) atomicAdd(&hist[__float_as_uint(c) >> 20], 1);
-    }
-    __syncthreads();
-    // lowest bucket whose suffix count fits in MAXC
-    {
-        int sum = 0;
-        for (int b = 0; b < NBUCKET / NTS; ++b) sum += hist[tid * (NBUCKET / NTS) + b];
-        psum[tid] = sum;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        constexpr int CH = NBUCKET / NTS;
-        int tot = 0;
-        for (int i = 0; i < NTS; ++i) tot += psum[i];
-        int acc = 0, cut = NBUCKET;                 // buckets >= cut are kept
-        int i = NTS - 1;
-        while (i >= 0 && acc + psum[i] <= MAXC) {   // whole chunks from the top
-            acc += psum[i];
-            cut = i * CH;
-            --i;
-        }
-        if (i >= 0) {                               // then single buckets
-            for (int b = i * CH + CH - 1; b >= i * CH; --b) {
-                if (acc + hist[b] > MAXC) break;
-                acc += hist[b];
-                cut = b;
+    // every candidate: f(value, raster index)
+    auto each_cand = [&](auto f) {
+        if (LIST && nlist <= cap) {
+            for (uint32_t i = tid; i < nlist; i += NTS) f(__uint_as_float(list[2 * i]), list[2 * i + 1]);
+        } else {
+            for (int i = tid; i < npix; i += NTS) {
+                const int y = y0 + i / tw, x = x0 + i % tw;
+                float c;
+                if (stamp_cand(a, y, x, sky, c)) f(c, (uint32_t)((int64_t)y * a.W + x));
             }
         }
-        cutoff = cut;
-        dropped = tot - acc;
-    }
-    __syncthreads();
-    for (int i = tid; i < npix; i += NTS) {
-        const int y = y0 + i / tw, x = x0 + i % tw;
-        float c;
-        if (is_cand(y, x, c) && (int)(__float_as_uint(c) >> 20) >= cutoff) {
-            const int slot = atomicAdd(&ncand, 1);
-            // brightest first, raster index breaking ties (c > 0)
-            keys[slot] = ((unsigned long long)(0xFFFFFFFFu - __float_as_uint(c)) << 32) |
-                         (unsigned int)((int64_t)y * a.W + x);
+    };
+    if (LIST && nlist <= MAXC) {
+        if (tid == 0) { cutoff = 0; dropped = 0; }      // every candidate fits
+    } else {
+        each_cand([&](float c, uint32_t) { atomicAdd(&hist[__float_as_uint(c) >> 20], 1); });
+        __syncthreads();
+        // lowest bucket whose suffix count fits in MAXC
+        {
+            int sum = 0;
+            for (int b = 0; b < NBUCKET / NTS; ++b) sum += hist[tid * (NBUCKET / NTS) + b];
+            psum[tid] = sum;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            constexpr int CH = NBUCKET / NTS;
+            int tot = 0;
+            for (int i = 0; i < NTS; ++i) tot += psum[i];
+            int acc = 0, cut = NBUCKET;                 // buckets >= cut are kept
+            int i = NTS - 1;
+            while (i >= 0 && acc + psum[i] <= MAXC) {   // whole chunks from the top
+                acc += psum[i];
+                cut = i * CH;
+                --i;
+            }
+            if (i >= 0) {                               // then single buckets
+                for (int b = i * CH + CH - 1; b >= i * CH; --b) {
+                    if (acc + hist[b] > MAXC) break;
+                    acc += hist[b];
+                    cut = b;
+                }
+            }
+            cutoff = cut;
+            dropped = tot - acc;
         }
     }
+    __syncthreads();
+    each_cand([&](float c, uint32_t idx) {
+        if ((int)(__float_as_uint(c) >> 20) >= cutoff) {
+            const int slot = atomicAdd(&ncand, 1);
+            // brightest first, raster index breaking ties (c > 0)
+            keys[slot] = ((unsigned long long)(0xFFFFFFFFu - __float_as_uint(c)) << 32) | idx;
+        }
+    });
     __syncthreads();
     const int nc = ncand;
     int m2 = 1;
@@ -1078,32 +1303,31 @@ __global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a) {
             __syncthreads();
         }
     }
-    // walk the ranking WW candidates at a time, one per walking wave
-    float *ws = sst + (size_t)(wave < WW ? wave : 0) * (2 * npx + 256);
+    // walk the ranking WW candidates at a time, one per wave
+    float *ws = sbuf[wave];
     for (int k0 = 0; k0 < nc; k0 += WW) {
         if (nacc >= a.S) break;                 // uniform: shared, read after a barrier
         const int k = k0 + wave;
         int ok = 0;
         float med = 0.f;
-        if (wave < WW && k < nc) {
+        if (k < nc) {
             const unsigned int idx = (unsigned int)(keys[k] & 0xFFFFFFFFull);
             const int y = idx / a.W, x = idx % a.W;
+            const int64_t o0 = (int64_t)(y - r) * P + x - r, o = (int64_t)y * P + x;
             int bad = 0;
-            for (int i = lane; i < npx; i += 64) {
-                const int64_t o = (int64_t)(y - r + i / n) * P + (x - r + i % n);
-                bad |= a.rmask[o] | a.smask[o];
-                ws[i] = a.ref[o];
+#pragma unroll
+            for (int j = 0; j < PXL; ++j) {
+                const int i = min(lane + 64 * j, npx - 1);
+                const int64_t oi = o0 + (int64_t)(i / n) * P + i % n;
+                bad |= a.rmask[oi] | a.smask[oi];
             }
             if (!__any(bad)) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                med = border_median_wave(ws, n, ws + 2 * npx, lane);
-                const int64_t o = (int64_t)y * P + x;
+                med = border_median_wave(a.ref + o0, P, n, ws, lane);
                 const float v = a.ref[o], vv = a.rvar[o];
                 ok = vv > 0.f && (v - med) / sqrtf(vv) >= a.snr_min;
             }
         }
-        if (lane == 0 && wave < WW) { flag[wave] = ok; fmed[wave] = med; }
+        if (lane == 0) { flag[wave] = ok; fmed[wave] = med; }
         __syncthreads();
         if (tid == 0) {
             for (int w = 0; w < WW && nacc < a.S; ++w) {
@@ -1118,29 +1342,36 @@ __global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a) {
         __syncthreads();
     }
     if (tid == 0 && nacc < a.S && dropped > 0) atomicAdd(a.overflow, 1);
-    // stamps: one walking wave per kept stamp
-    for (int s = wave; s < a.S && wave < WW; s += WW) {
+    // stamps: one wave per kept stamp, its pixels in registers
+    for (int s = wave; s < a.S; s += WW) {
         const int64_t base = ((int64_t)t * a.S + s) * npx * 2;
         uint8_t ok = 0;
         if (s < nacc) {
-            const int y = acc_y[s], x = acc_x[s];
-            for (int i = lane; i < npx; i += 64) {
-                const int64_t o = (int64_t)(y - r + i / n) * P + (x - r + i % n);
-                ws[i] = a.ref[o];
-                ws[npx + i] = a.sci[o];
+            const int64_t o0 = (int64_t)(acc_y[s] - r) * P + acc_x[s] - r;
+            float pr[PXL], ps[PXL];
+#pragma unroll
+            for (int j = 0; j < PXL; ++j) {
+                const int i = min(lane + 64 * j, npx - 1);
+                const int64_t oi = o0 + (int64_t)(i / n) * P + i % n;
+                pr[j] = a.ref[oi];
+                ps[j] = a.sci[oi];
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
             const float mr = acc_m[s];
-            const float ms = border_median_wave(ws + npx, n, ws + 2 * npx, lane);
+            const float ms = border_median_wave(a.sci + o0, P, n, ws, lane);
             float sum = 0.f;
-            for (int i = lane; i < npx; i += 64) sum += ws[i] - mr;
+#pragma unroll
+            for (int j = 0; j < PXL; ++j)
+                if (lane + 64 * j < npx) sum += pr[j] - mr;
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
             if (sum > 0.f) {
                 const float inv = STAMP_SCALE / sum;
-                for (int i = lane; i < npx; i += 64) {
-                    a.X[base + 2 * i] = (bf16)((ws[i] - mr) * inv);
-                    a.X[base + 2 * i + 1] = (bf16)((ws[npx + i] - ms) * inv);
+#pragma unroll
+                for (int j = 0; j < PXL; ++j) {
+                    const int i = lane + 64 * j;
+                    if (i < npx) {
+                        a.X[base + 2 * i] = (bf16)((pr[j] - mr) * inv);
+                        a.X[base + 2 * i + 1] = (bf16)((ps[j] - ms) * inv);
+                    }
                 }
                 ok = 1;
             }
@@ -1542,10 +1773,25 @@ int argus_extract_stamps(argus_ctx *ctx, argus_dims d, const float *ref, const f
     a.pitch = d.pitch; a.W = d.width; a.H = d.height; a.TX = tiles_x; a.TY = tiles_y;
     a.S = stamps_per_tile; a.r = half; a.snr_min = snr_min;
     const int npx = (2 * half + 1) * (2 * half + 1);
-    size_t lds = (size_t)WW * (2 * npx + 256) * sizeof(float);
-    ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute((const void *)stamps_kernel,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(stamps_kernel, dim3(tiles_x * tiles_y), dim3(NTS), lds, ctx->stream, a);
+    const int T = tiles_x * tiles_y;
+    // the scratch is 32-bit words in each tile's part of X
+    if ((size_t)a.S * npx >= SC_MIN && (uintptr_t)X % 4 == 0) {
+        const uint32_t cap = (uint32_t)((a.S * npx - SC_LIST) / 2);
+        const int tw = (d.width + tiles_x - 1) / tiles_x, th = (d.height + tiles_y - 1) / tiles_y;
+        const int want = SC_PX / tw > 1 ? SC_PX / tw : 1;
+        // (the grid's second axis holds at most 65535 row groups)
+        const int rows = want > (th + 65534) / 65535 ? want : (th + 65534) / 65535;
+        const dim3 g(T, (th + rows - 1) / rows);
+        hipStream_t st = ctx->stream;
+        hipLaunchKernelGGL(stamp_clear_kernel, dim3(T), dim3(SCH), 0, st, a);
+        hipLaunchKernelGGL(stamp_hist_kernel<1>, g, dim3(SCH), 0, st, a, rows);
+        hipLaunchKernelGGL(stamp_hist_kernel<2>, g, dim3(SCH), 0, st, a, rows);
+        hipLaunchKernelGGL(stamp_hist_kernel<3>, g, dim3(SCH), 0, st, a, rows);
+        hipLaunchKernelGGL(stamp_cand_kernel, g, dim3(SCH), 0, st, a, rows, cap);
+        hipLaunchKernelGGL(stamps_kernel<true>, dim3(T), dim3(NTS), 0, st, a, cap);
+    } else {
+        hipLaunchKernelGGL(stamps_kernel<false>, dim3(T), dim3(NTS), 0, ctx->stream, a, 0u);
+    }
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
