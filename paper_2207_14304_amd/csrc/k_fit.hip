@@ -26,110 +26,134 @@ namespace {
 // B_k(u,v) = exp(-(u^2+v^2)/2s^2) u^i v^j; B_0 -> unit sum; k>=1 with i, j
 // even -> B_k - (sum B_k) B_0; k >= 1 -> unit L2 norm.  In separable form
 // B'_k = alpha_k f_{g,i}(u) f_{g,j}(v) + beta_k B_0raw.
-__global__ void basis_tables_kernel(argus_kernel_spec s, BasisTables *T) {
-    __shared__ int kg[32], ki[32], kj[32], kp[32];
+//
+// One workgroup of 16 waves, a wave per basis function for the sums over the
+// grid, from the 1-D factors in LDS; part of the first fit of a spec (one
+// thread per basis function with two exponentials and two powers a sample took
+// 325 us at h = 7, 740 us at h = 10; now 13 and 17 us).
+constexpr int BT_THREADS = 1024;
+constexpr int BT_PMAX = 7;                 // powers 0..6
+
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+__global__ __launch_bounds__(BT_THREADS) void basis_tables_kernel(argus_kernel_spec s, BasisTables *T) {
+    __shared__ int kg[32], ki[32], kj[32], kp[32], s_nb;
+    __shared__ double f[4][BT_PMAX][32];   // exp(-u^2/2s^2) u^i, index u + h
     __shared__ double alpha[32], beta[32];
-    __shared__ double S0;
     const int h = s.half_width, K = 2 * h + 1;
-    if (threadIdx.x == 0) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (tid == 0) {
         int k = 0, p = 0;
         for (int g = 0; g < s.n_gauss; ++g)
-            for (int i = 0; i <= s.degree[g]; ++i, ++p)
+            for (int i = 0; i <= s.degree[g]; ++i, ++p) {
                 for (int j = 0; j <= s.degree[g] - i; ++j, ++k) {
                     kg[k] = g; ki[k] = i; kj[k] = j; kp[k] = p;
                 }
+                T->ipow[p] = i;
+            }
+        s_nb = k;
         T->nb = k;
         T->nplanes = p;
         T->h = h;
-        double sum = 0.0;
-        double is2 = 1.0 / (2.0 * s.sigma[0] * s.sigma[0]);
-        for (int v = -h; v <= h; ++v)
-            for (int u = -h; u <= h; ++u) sum += exp(-(double)(u * u + v * v) * is2);
-        S0 = sum;
+    }
+    if (tid < 4 * 32) {
+        const int g = tid >> 5, u = (tid & 31) - h;
+        if (g < s.n_gauss && u <= h) {
+            const double is2 = 1.0 / (2.0 * s.sigma[g] * s.sigma[g]);
+            const double e = exp(-(double)(u * u) * is2);
+            double pw = 1.0;                   // u^i, exact
+            for (int i = 0; i < BT_PMAX; ++i, pw *= (double)u) f[g][i][u + h] = e * pw;
+        }
     }
     __syncthreads();
-    const int nb = T->nb;
-    int k = threadIdx.x;
-    if (k < nb) {
-        double is2 = 1.0 / (2.0 * s.sigma[kg[k]] * s.sigma[kg[k]]);
-        double is20 = 1.0 / (2.0 * s.sigma[0] * s.sigma[0]);
+    const int nb = s_nb;
+    // every wave forms B_0's sum itself
+    double S0 = 0.0;
+    for (int t = lane; t < K * K; t += 64) S0 += f[0][0][t % K] * f[0][0][t / K];
+    S0 = wave_sum(S0);
+    for (int k = wv; k < nb; k += BT_THREADS / 64) {
+        const double *fu = f[kg[k]][ki[k]], *fv = f[kg[k]][kj[k]];
         double raw_sum = 0.0;
-        for (int v = -h; v <= h; ++v)
-            for (int u = -h; u <= h; ++u)
-                raw_sum += exp(-(double)(u * u + v * v) * is2) * pow((double)u, ki[k]) *
-                           pow((double)v, kj[k]);
-        bool even = (ki[k] % 2 == 0) && (kj[k] % 2 == 0);
-        double c0 = (k >= 1 && even) ? raw_sum / S0 : 0.0;   // subtract c0 * B_0raw
+        for (int t = lane; t < K * K; t += 64) raw_sum += fu[t % K] * fv[t / K];
+        raw_sum = wave_sum(raw_sum);
+        const bool even = (ki[k] % 2 == 0) && (kj[k] % 2 == 0);
+        const double c0 = (k >= 1 && even) ? raw_sum / S0 : 0.0;   // subtract c0 * B_0raw
         double nrm = 0.0;
-        for (int v = -h; v <= h; ++v)
-            for (int u = -h; u <= h; ++u) {
-                double b = exp(-(double)(u * u + v * v) * is2) * pow((double)u, ki[k]) *
-                           pow((double)v, kj[k]) - c0 * exp(-(double)(u * u + v * v) * is20);
-                nrm += b * b;
-            }
-        double a, be;
-        if (k == 0) {
-            a = 1.0 / S0;
-            be = 0.0;
-        } else {
-            a = 1.0 / sqrt(nrm);
-            be = -c0 * a;
+        for (int t = lane; t < K * K; t += 64) {
+            const double b = fu[t % K] * fv[t / K] - c0 * (f[0][0][t % K] * f[0][0][t / K]);
+            nrm += b * b;
         }
-        alpha[k] = a;
-        beta[k] = be;
-        T->gam[k] = (float)(be * S0);     // C'_k = alpha_k conv_k + (beta_k / alpha_0) C'_0
-        T->kpl[k] = kp[k];
-        for (int v = -h; v <= h; ++v)
-            T->colf[k][v + h] = (float)(a * exp(-(double)(v * v) * is2) * pow((double)v, kj[k]));
+        nrm = wave_sum(nrm);
+        const double a = k == 0 ? 1.0 / S0 : 1.0 / sqrt(nrm), be = k == 0 ? 0.0 : -c0 * a;
+        if (lane == 0) {
+            alpha[k] = a;
+            beta[k] = be;
+            T->gam[k] = (float)(be * S0);     // C'_k = alpha_k conv_k + (beta_k / alpha_0) C'_0
+            T->kpl[k] = kp[k];
+        }
+        if (lane < K) {
+            T->colf[k][lane] = (float)(a * fv[lane]);
+            if (kj[k] == 0) T->rowf[kp[k]][lane] = (float)fu[lane];      // one j = 0 per plane
+        }
     }
     __syncthreads();
     // 2-D normalised basis for the kernel expansion
-    for (int idx = threadIdx.x; idx < nb * K * K; idx += blockDim.x) {
-        int kk = idx / (K * K), t = idx % (K * K);
-        int v = t / K - h, u = t % K - h;
-        double is2 = 1.0 / (2.0 * s.sigma[kg[kk]] * s.sigma[kg[kk]]);
-        double is20 = 1.0 / (2.0 * s.sigma[0] * s.sigma[0]);
-        double b = exp(-(double)(u * u + v * v) * is2) * pow((double)u, ki[kk]) * pow((double)v, kj[kk]);
-        T->b2d[kk][t] = alpha[kk] * b + beta[kk] * exp(-(double)(u * u + v * v) * is20);
-    }
-    // row filters per plane (g, i)
-    if (threadIdx.x < 32) {
-        int p = threadIdx.x;
-        int pp = 0;
-        for (int g = 0; g < s.n_gauss; ++g)
-            for (int i = 0; i <= s.degree[g]; ++i, ++pp)
-                if (pp == p) {
-                    T->ipow[p] = i;
-                    double is2 = 1.0 / (2.0 * s.sigma[g] * s.sigma[g]);
-                    for (int u = -h; u <= h; ++u)
-                        T->rowf[p][u + h] = (float)(exp(-(double)(u * u) * is2) * pow((double)u, i));
-                }
+    for (int idx = tid; idx < nb * K * K; idx += BT_THREADS) {
+        const int k = idx / (K * K), t = idx % (K * K);
+        const int v = t / K, u = t % K;
+        T->b2d[k][t] = alpha[k] * (f[kg[k]][ki[k]][u] * f[kg[k]][kj[k]][v]) +
+                       beta[k] * (f[0][0][u] * f[0][0][v]);
     }
 }
 
-// Sum consecutive groups of partial vectors in a fixed order (deterministic).
+// Sum consecutive groups of partial vectors in a fixed order (deterministic);
+// 8 loads in flight per thread (the adds stay in order).
 __global__ void sum_parts_kernel(const double *in, int stride, int n_in, int group, double *out) {
     int e = blockIdx.x * blockDim.x + threadIdx.x;
     int set = blockIdx.y;
     if (e >= stride) return;
-    int j0 = set * group, j1 = min(j0 + group, n_in);
+    const int j0 = set * group, j1 = min(j0 + group, n_in);
+    const double *p = in + e;
     double s = 0.0;
-    for (int j = j0; j < j1; ++j) s += in[(size_t)j * stride + e];
+    int j = j0;
+    for (; j + 8 <= j1; j += 8) {
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = p[(size_t)(j + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += v[i];
+    }
+    for (; j < j1; ++j) s += p[(size_t)j * stride];
     out[(size_t)set * stride + e] = s;
 }
 
-// K_m = sum_k a_{k nP + m} B_k (FP64), bg_m = a_{nb nP + m}
-__global__ void expand_kernel(const BasisTables *T, const double *coeffs, int n, int nP, int nPb,
-                              float *stamps, float *bg) {
+// K_m = sum_k a_{k nP + m} B_k (FP64), bg_m = a_{nb nP + m}: a workgroup per
+// 64 samples of a stamp, the basis values of 31 functions in flight (the sum
+// over k stays in order; with a workgroup per stamp and one load at a time
+// the launch took 27 us at 21 x 21, now 6 us)
+__global__ __launch_bounds__(64) void expand_kernel(const BasisTables *T, const double *coeffs,
+                                                    int n, int nP, int nPb, int K, int nb,
+                                                    float *stamps, float *bg) {
     const int s = blockIdx.x / nP, m = blockIdx.x % nP;
-    const int K = 2 * T->h + 1, nb = T->nb;
     const double *a = coeffs + (size_t)s * n;
-    for (int t = threadIdx.x; t < K * K; t += blockDim.x) {
-        double acc = 0.0;
-        for (int k = 0; k < nb; ++k) acc += a[k * nP + m] * T->b2d[k][t];
+    const int t = blockIdx.y * 64 + threadIdx.x;
+    if (t < K * K) {
+        double b[ARGUS_MAX_NB], c[ARGUS_MAX_NB], acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < ARGUS_MAX_NB; ++k) {
+            const int kc = min(k, nb - 1);
+            b[k] = T->b2d[kc][t];
+            c[k] = a[kc * nP + m];
+        }
+#pragma unroll
+        for (int k = 0; k < ARGUS_MAX_NB; ++k)
+            if (k < nb) acc += c[k] * b[k];
         stamps[((size_t)s * nP + m) * K * K + t] = (float)acc;
     }
-    if (threadIdx.x == 0 && m < nPb) bg[(size_t)s * nPb + m] = (float)a[nb * nP + m];
+    if (t == 0 && m < nPb) bg[(size_t)s * nPb + m] = (float)a[nb * nP + m];
 }
 
 template <int D>
@@ -178,7 +202,7 @@ int fit_launch_d(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, Fi
 }  // namespace
 
 int launch_basis_tables_to(argus_ctx *ctx, const argus_kernel_spec *spec, BasisTables *dst) {
-    hipLaunchKernelGGL(basis_tables_kernel, dim3(1), dim3(256), 0, ctx->stream, *spec, dst);
+    hipLaunchKernelGGL(basis_tables_kernel, dim3(1), dim3(BT_THREADS), 0, ctx->stream, *spec, dst);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
@@ -189,7 +213,7 @@ int launch_basis_tables(argus_ctx *ctx, const argus_kernel_spec *spec) {
     for (int g = 0; same && g < spec->n_gauss; ++g)
         same = o.sigma[g] == spec->sigma[g] && o.degree[g] == spec->degree[g];
     if (same) return ARGUS_OK;
-    hipLaunchKernelGGL(basis_tables_kernel, dim3(1), dim3(256), 0, ctx->stream, *spec, ctx->tables);
+    hipLaunchKernelGGL(basis_tables_kernel, dim3(1), dim3(BT_THREADS), 0, ctx->stream, *spec, ctx->tables);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     ctx->tables_spec = *spec;
     ctx->tables_valid = true;
@@ -317,8 +341,10 @@ int launch_expand(argus_ctx *ctx, const argus_kernel_spec *spec, const double *c
     int n, ns;
     argus_kernel_dims(spec, &n, &ns);
     int nP = argus_npoly(spec->spatial_degree), nPb = argus_npoly(spec->bg_degree);
-    hipLaunchKernelGGL(expand_kernel, dim3(ns * nP), dim3(256), 0, ctx->stream,
-                       (const BasisTables *)ctx->tables, coeffs, n, nP, nPb, stamps, bg);
+    const int K = 2 * spec->half_width + 1;
+    hipLaunchKernelGGL(expand_kernel, dim3(ns * nP, (K * K + 63) / 64), dim3(64), 0, ctx->stream,
+                       (const BasisTables *)ctx->tables, coeffs, n, nP, nPb, K, argus_nbasis(spec),
+                       stamps, bg);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
