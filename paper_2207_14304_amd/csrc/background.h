@@ -51,3 +51,36 @@ __device__ __forceinline__ float bg_at(const BgGrid &g, int x, int y) {
     const float bot = g10 + tx * (g11 - g10);
     return top + ty * (bot - top);
 }
+
+// N adjacent columns of the same evaluation for pixels taken row by row: the
+// columns' nodes and weights are kept, and their values on the two node rows
+// until the row leaves the pair.
+template <int N>
+struct BgColumns {
+    int ix[N];
+    float tx[N], top[N], bot[N];
+    int iy0 = -1;
+    __device__ __forceinline__ BgColumns(const BgGrid &g, int x) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) bg_axis(x + e, g.box, g.gx, g.cxl, ix[e], tx[e]);
+    }
+    __device__ __forceinline__ void at(const BgGrid &g, int y, float (&o)[N]) {
+        int iy;
+        float ty;
+        bg_axis(y, g.box, g.gy, g.cyl, iy, ty);
+        if (iy != iy0) {
+            iy0 = iy;
+            const int iy1 = iy + 1 < g.gy ? iy + 1 : iy;
+            const float *r0 = g.grid + (size_t)iy * g.gx, *r1 = g.grid + (size_t)iy1 * g.gx;
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const int i1 = ix[e] + 1 < g.gx ? ix[e] + 1 : ix[e];
+                const float g00 = r0[ix[e]], g01 = r0[i1], g10 = r1[ix[e]], g11 = r1[i1];
+                top[e] = g00 + tx[e] * (g01 - g00);
+                bot[e] = g10 + tx[e] * (g11 - g10);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < N; ++e) o[e] = top[e] + ty * (bot[e] - top[e]);
+    }
+};

@@ -2,12 +2,12 @@
 //
 // bg_cell: one workgroup per box x box cell (box <= 64, so a thread holds at
 //   most 16 pixels in registers).  The cell's level is the exact median of
-//   its unmasked values: a 4-pass radix select on order-preserving 32-bit keys
-//   of the FP32 values (8 bits per pass, LDS histogram, one wave scans it),
-//   and for an even count the next key by a count and a minimum; the mean of
-//   the middle pair is formed in FP64 and rounded once.
+//   its unmasked values: a radix select on order-preserving 32-bit keys of the
+//   FP32 values (digits of 11, 11 and 10 bits, LDS histograms), and for an even
+//   count the next key by a minimum; the mean of the middle pair is formed in
+//   FP64 and rounded once.
 // bg_filter: one thread per cell, median of the present levels of its 3 x 3
-//   neighbourhood (insertion sort of at most 9 values).
+//   neighbourhood (a sorting network over 9 values).
 // bg_map: bilinear interpolation between cell centres to every pixel (only
 //   when the caller asks for the full-resolution map; detection evaluates the
 //   same interpolation on the fly).
@@ -32,113 +32,152 @@ struct CellArgs {
     float *levels;
     int64_t pitch;
     int W, H, box, gx, gy;
+    int vec;                           // 16-byte rows of cal, 4-byte rows of mask
 };
 
-__device__ int block_sum_i(int v, int *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int s = 0;
-    for (int i = 0; i < NTHR / 64; ++i) s += red[i];
-    return s;
-}
-
+// What bounds this kernel is instruction issue and LDS atomics, not its 5
+// bytes per pixel (50 us on the full frame).  Whole cells of 32 or 64 columns
+// on aligned planes read 4 pixels a lane with no divisions; a sky's keys share
+// their first digit, so there a wave adds its first lane's digit with one
+// atomic (64 lanes on one address take 64 turns); each thread clears the bins
+// it scans, so a digit takes three barriers.  Full frame, 64 x 64 cells: 267 ->
+// 110 us, against four 8-bit digits scanned by one wave.
 __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
-    __shared__ int hist[256];
-    __shared__ int red[NTHR / 64];
-    __shared__ uint32_t sel[2];          // selected prefix, remaining rank
+    constexpr int NB = 2048, PER = NB / NTHR;
+    __shared__ __align__(16) int hist[NB];
+    __shared__ int wsum[NTHR / 64];
+    __shared__ uint32_t sel[3];          // selected digit, rank within it, its count
     __shared__ uint32_t kmin;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int ci = blockIdx.x % a.gx, cj = blockIdx.x / a.gx;
     const int x0 = ci * a.box, y0 = cj * a.box;
     const int cw = min(a.box, a.W - x0), ch = min(a.box, a.H - y0);
     const int np = cw * ch;
     uint32_t key[MAXV];
-    int nv = 0;
+    uint32_t okbits = 0;
     // every load of a thread is issued before any is used
     float v[MAXV];
     uint8_t m[MAXV];
+    if (a.vec && (cw == 64 || cw == 32)) {
+        const int lg = cw == 64 ? 4 : 3, row = tid >> lg, c4 = (tid & ((1 << lg) - 1)) * 4;
+        const int step = NTHR >> lg;       // rows of a pass over the workgroup
+        float4 q[4];
+        uint32_t mm[4];
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {
-        const int i = tid + k * NTHR;
-        const int ii = i < np ? i : 0;
-        const int64_t o = (int64_t)(y0 + ii / cw) * a.pitch + x0 + ii % cw;
-        v[k] = a.cal[o];
-        m[k] = a.mask[o];
-    }
+        for (int k = 0; k < 4; ++k) {
+            const int64_t o = (int64_t)(y0 + min(row + k * step, ch - 1)) * a.pitch + x0 + c4;
+            q[k] = *(const float4 *)(a.cal + o);
+            mm[k] = *(const uint32_t *)(a.mask + o);
+        }
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {
-        const int i = tid + k * NTHR;
-        const bool ok = i < np && m[k] == 0;
-        key[k] = ok ? f2key(v[k]) : 0u;      // 0 never equals a selected prefix with ok = false
-        nv += ok ? 1 : 0;
-    }
-    uint32_t okbits = 0;
+        for (int k = 0; k < 4; ++k) {
+            const float e[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+            const bool in = row + k * step < ch;
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {
-        const int i = tid + k * NTHR;
-        if (i < np && m[k] == 0) okbits |= 1u << k;
-    }
-    const int n = block_sum_i(nv, red);
-    if (n == 0) {
-        if (tid == 0) a.levels[blockIdx.x] = __builtin_nanf("");
-        return;
-    }
-    // k-th smallest key (0-based): the lower middle for an even count
-    const uint32_t k1 = (uint32_t)((n - 1) / 2);
-    if (tid == 0) { sel[0] = 0u; sel[1] = k1; }
-    uint32_t pmask = 0u;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0;
-        __syncthreads();
-        const uint32_t prefix = sel[0];
-#pragma unroll
-        for (int k = 0; k < MAXV; ++k)
-            if (((okbits >> k) & 1u) && (key[k] & pmask) == prefix)
-                atomicAdd(&hist[(key[k] >> shift) & 255u], 1);
-        __syncthreads();
-        if (tid < 64) {
-            // lane l owns bins 4l .. 4l+3; inclusive scan of the lane sums
-            const int h0 = hist[4 * tid], h1 = hist[4 * tid + 1], h2 = hist[4 * tid + 2],
-                      h3 = hist[4 * tid + 3];
-            const int s = h0 + h1 + h2 + h3;
-            int inc = s;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(inc, off);
-                if (tid >= off) inc += t;
-            }
-            const uint32_t r = sel[1];
-            const int before = inc - s;
-            if ((uint32_t)before <= r && r < (uint32_t)inc) {
-                // the rank falls in this lane's four bins
-                int acc = before, d = 4 * tid;
-                const int hh[4] = {h0, h1, h2, h3};
-                for (int q = 0; q < 4; ++q) {
-                    if (r < (uint32_t)(acc + hh[q])) { d = 4 * tid + q; break; }
-                    acc += hh[q];
-                }
-                sel[0] = prefix | ((uint32_t)d << shift);
-                sel[1] = r - (uint32_t)acc;
+            for (int j = 0; j < 4; ++j) {
+                v[4 * k + j] = e[j];
+                if (in && ((mm[k] >> (8 * j)) & 0xffu) == 0) okbits |= 1u << (4 * k + j);
             }
         }
-        pmask |= 255u << shift;
-        __syncthreads();
+    } else {
+#pragma unroll
+        for (int k = 0; k < MAXV; ++k) {
+            const int i = tid + k * NTHR;
+            const int ii = i < np ? i : 0;
+            const int64_t o = (int64_t)(y0 + ii / cw) * a.pitch + x0 + ii % cw;
+            v[k] = a.cal[o];
+            m[k] = a.mask[o];
+        }
+#pragma unroll
+        for (int k = 0; k < MAXV; ++k)
+            if (tid + k * NTHR < np && m[k] == 0) okbits |= 1u << k;
     }
-    const uint32_t kk1 = sel[0];
+#pragma unroll
+    for (int k = 0; k < MAXV; ++k) key[k] = f2key(v[k]);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) hist[tid + i * NTHR] = 0;
+    if (tid == 0) kmin = 0xffffffffu;
+    __syncthreads();
+    // k-th smallest key (0-based): the lower middle for an even count
+    uint32_t prefix = 0, rank = 0;
+    int n = 0;
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+        const uint32_t dmask = pass == 2 ? 1023u : 2047u;
+#pragma unroll
+        for (int k = 0; k < MAXV; ++k) {
+            const bool ok = (okbits >> k) & 1u;
+            const uint32_t d = (key[k] >> shift) & dmask;
+            if (pass == 0) {
+                const uint64_t act = __ballot(ok);
+                if (act) {
+                    const uint32_t d0 =
+                        (uint32_t)__builtin_amdgcn_readlane((int)d, __builtin_ctzll(act));
+                    const bool same = ok && d == d0;
+                    const uint64_t sm = __ballot(same);
+                    if (lane == 0) atomicAdd(&hist[d0], __popcll(sm));
+                    if (ok && !same) atomicAdd(&hist[d], 1);
+                }
+            } else if (ok && key[k] >> (pass == 1 ? 21 : 10) == prefix) {
+                atomicAdd(&hist[d], 1);
+            }
+        }
+        __syncthreads();
+        // each thread owns PER bins: inclusive scan of the sums, bins cleared
+        int h[PER], s = 0;
+#pragma unroll
+        for (int i = 0; i < PER; i += 4) {
+            const int4 q = *(const int4 *)&hist[PER * tid + i];
+            *(int4 *)&hist[PER * tid + i] = make_int4(0, 0, 0, 0);
+            h[i] = q.x; h[i + 1] = q.y; h[i + 2] = q.z; h[i + 3] = q.w;
+            s += q.x + q.y + q.z + q.w;
+        }
+        int inc = s;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(inc, off);
+            if (lane >= off) inc += t;
+        }
+        if (lane == 63) wsum[tid >> 6] = inc;
+        __syncthreads();
+        int before = inc - s, tot = 0;
+        for (int w = 0; w < NTHR / 64; ++w) {
+            if (w < (tid >> 6)) before += wsum[w];
+            tot += wsum[w];
+        }
+        if (pass == 0) {
+            n = tot;
+            if (n == 0) {
+                if (tid == 0) a.levels[blockIdx.x] = __builtin_nanf("");
+                return;
+            }
+            rank = (uint32_t)((n - 1) / 2);
+        }
+        if ((uint32_t)before <= rank && rank < (uint32_t)(before + s)) {
+            int acc = before;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if ((uint32_t)acc <= rank && rank < (uint32_t)(acc + h[i])) {
+                    sel[0] = (uint32_t)(PER * tid + i);
+                    sel[1] = rank - (uint32_t)acc;
+                    sel[2] = (uint32_t)h[i];
+                }
+                acc += h[i];
+            }
+        }
+        __syncthreads();
+        prefix = prefix << (pass == 2 ? 10 : 11) | sel[0];
+        rank = sel[1];
+    }
+    const uint32_t kk1 = prefix;
     float med;
     if (n & 1) {
         med = key2f(kk1);
     } else {
-        // upper middle: the same key if it repeats past rank k1, else the
+        // upper middle: the same key if it repeats past the rank, else the
         // smallest key above it
-        int le = 0;
-#pragma unroll
-        for (int k = 0; k < MAXV; ++k) le += (((okbits >> k) & 1u) && key[k] <= kk1) ? 1 : 0;
-        if (tid == 0) kmin = 0xffffffffu;
-        const int nle = block_sum_i(le, red);
         uint32_t kk2 = kk1;
-        if ((uint32_t)nle < k1 + 2u) {
+        if (rank + 1 >= sel[2]) {
             uint32_t mn = 0xffffffffu;
 #pragma unroll
             for (int k = 0; k < MAXV; ++k)
@@ -147,7 +186,7 @@ __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
                 const uint32_t t = (uint32_t)__shfl_xor((int)mn, off);
                 mn = t < mn ? t : mn;
             }
-            if ((tid & 63) == 0) atomicMin(&kmin, mn);
+            if (lane == 0) atomicMin(&kmin, mn);
             __syncthreads();
             kk2 = kmin;
         }
@@ -156,33 +195,63 @@ __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
     if (tid == 0) a.levels[blockIdx.x] = med;
 }
 
+// An odd-even transposition network over 9 values, absent ones +inf at the
+// end (values in registers: a sort with run-time indices would live in
+// scratch memory).
 __global__ void bg_filter_kernel(const float *levels, float *grid, int gx, int gy) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= gx * gy) return;
     const int i = c % gx, j = c / gx;
     float v[9];
     int n = 0;
-    for (int dj = -1; dj <= 1; ++dj)
-        for (int di = -1; di <= 1; ++di) {
-            const int ii = i + di, jj = j + dj;
-            if (ii < 0 || ii >= gx || jj < 0 || jj >= gy) continue;
-            const float l = levels[jj * gx + ii];
-            if (l != l) continue;                           // no level
-            int p = n++;
-            while (p > 0 && v[p - 1] > l) { v[p] = v[p - 1]; --p; }
-            v[p] = l;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        const int ii = i + t % 3 - 1, jj = j + t / 3 - 1;
+        const bool in = ii >= 0 && ii < gx && jj >= 0 && jj < gy;
+        const float l = levels[in ? jj * gx + ii : c];
+        const bool has = in && l == l;                      // NaN: no level
+        v[t] = has ? l : __builtin_inff();
+        n += has ? 1 : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < 9; ++r)
+#pragma unroll
+        for (int t = r & 1; t + 1 < 9; t += 2) {
+            const float lo = fminf(v[t], v[t + 1]), hi = fmaxf(v[t], v[t + 1]);
+            v[t] = lo;
+            v[t + 1] = hi;
         }
-    float out = 0.f;
-    if (n & 1) out = v[n / 2];
-    else if (n > 0) out = (float)(0.5 * ((double)v[n / 2 - 1] + (double)v[n / 2]));
-    grid[c] = out;
+    float a = 0.f, b = 0.f;                                 // the middle pair (n odd: a = b)
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        if (t == (n - 1) / 2) a = v[t];
+        if (t == n / 2) b = v[t];
+    }
+    grid[c] = n == 0 ? 0.f : (n & 1) ? b : (float)(0.5 * ((double)a + (double)b));
 }
 
+// Four columns x MAP_ROWS rows a thread: a column's node and weight are formed
+// once, and its values on the two node rows once per crossing of a cell centre,
+// so a pixel costs one subtraction, one FMA and its 4 bytes (139 -> 60 us on
+// the full frame against a pixel a thread).
+constexpr int MAP_ROWS = 16;
 __global__ __launch_bounds__(NTHR) void bg_map_kernel(BgGrid g, float *map, int64_t pitch, int W,
-                                                      int H) {
-    const int x = blockIdx.x * NTHR + threadIdx.x, y = blockIdx.y;
+                                                      int H, int vec) {
+    const int x = 4 * (blockIdx.x * NTHR + threadIdx.x), y0 = blockIdx.y * MAP_ROWS;
     if (x >= W) return;
-    map[(int64_t)y * pitch + x] = bg_at(g, x, y);
+    BgColumns<4> col(g, x);
+    for (int y = y0; y < min(y0 + MAP_ROWS, H); ++y) {
+        float o[4];
+        col.at(g, y, o);
+        float *p = map + (int64_t)y * pitch + x;
+        if (vec && x + 3 < W) {
+            *(float4 *)p = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x + e < W) p[e] = o[e];
+        }
+    }
 }
 
 }  // namespace
@@ -196,7 +265,8 @@ int launch_background(argus_ctx *ctx, argus_dims d, const float *cal, const uint
         if (rc) return rc;
         lev = (float *)ctx->ws;
     }
-    CellArgs a{cal, mask, lev, d.pitch, d.width, d.height, box, gx, gy};
+    const int vec = d.pitch % 4 == 0 && (uintptr_t)cal % 16 == 0 && (uintptr_t)mask % 4 == 0;
+    CellArgs a{cal, mask, lev, d.pitch, d.width, d.height, box, gx, gy, vec};
     argus_time_begin(ctx);
     hipLaunchKernelGGL(bg_cell_kernel, dim3(gx * gy), dim3(NTHR), 0, ctx->stream, a);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
@@ -207,8 +277,10 @@ int launch_background(argus_ctx *ctx, argus_dims d, const float *cal, const uint
     if (map) {
         BgGrid g = make_bg_grid(grid, box, d.width, d.height);
         argus_time_begin(ctx);
-        hipLaunchKernelGGL(bg_map_kernel, dim3((d.width + NTHR - 1) / NTHR, d.height), dim3(NTHR), 0,
-                           ctx->stream, g, map, d.pitch, d.width, d.height);
+        const int mvec = d.pitch % 4 == 0 && (uintptr_t)map % 16 == 0;
+        hipLaunchKernelGGL(bg_map_kernel,
+                           dim3((d.width + 4 * NTHR - 1) / (4 * NTHR), (d.height + MAP_ROWS - 1) / MAP_ROWS),
+                           dim3(NTHR), 0, ctx->stream, g, map, d.pitch, d.width, d.height, mvec);
         ARGUS_HIP_CHECK(ctx, hipGetLastError());
         argus_time_end(ctx, "background_map");
     }

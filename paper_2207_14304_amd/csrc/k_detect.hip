@@ -7,16 +7,17 @@
 //   each 256-pixel row segment.
 // scan_tiles: exclusive scan of the segment counts within 1024-count tiles,
 //   and each tile's total.
-// detect_emit: a wave takes 64 segments (one scan tile's), adds the totals of
-//   the tiles before theirs, and for each segment with candidates writes them
-//   in raster order at their offsets and measures the PSF flux in FP64; the
-//   first wave writes the candidate count.
+// detect_emit: a wave takes up to 64 segments (one scan tile's), adds the
+//   totals of the tiles before theirs, and for each segment with candidates
+//   writes them in raster order at their offsets and measures the PSF flux in
+//   FP64; the first wave writes the candidate count.
 //
 // Source mode (argus_detect_sources): the same kernels on a calibrated frame,
 // with D = cal - background evaluated from the filtered cell grid per pixel,
 // V the calibration's variance and its mask; sources also get the centroid
 // of max(D, 0) over the unmasked in-image 3 x 3 neighbourhood.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 #include "background.h"
@@ -26,7 +27,7 @@ namespace {
 constexpr int SEG = 256, ROWS = 16, NTHR = 256;   // a wave covers a 256-pixel row, 4 px a lane
 constexpr int LW = SEG + 8;                        // LDS row: [3] = x0-1, [4..259], [260] = x0+256
 constexpr int STILE = 1024;                        // counts per scan tile
-static_assert(STILE % 64 == 0, "a wave's 64 segments lie in one scan tile");
+static_assert(STILE % 64 == 0, "a wave's segments lie in one scan tile");
 
 struct DetArgs {
     const float *diff, *dvar;
@@ -44,6 +45,7 @@ struct DetArgs {
     int64_t pitch;
     int W, H, nsx, nseg, ntile, r, cap;
     int vec;                   // 16-byte aligned planes, pitch % 4 == 0
+    int group;                 // segments of an emitting wave (a power of two <= 64)
     float thr;
 };
 
@@ -68,6 +70,10 @@ __device__ __forceinline__ float snr_of(float D, float V, uint32_t m) {
     return (m != 0 || !(V > 0.f)) ? 0.f : D * __builtin_amdgcn_rsqf(V);
 }
 
+struct NoColumns {             // difference mode has no background
+    __device__ NoColumns(const BgGrid &, int) {}
+};
+
 template <bool SRC>
 __global__ __launch_bounds__(NTHR) void detect_map_kernel(DetArgs a) {
     __shared__ __align__(16) float s[ROWS + 2][LW];
@@ -81,46 +87,56 @@ __global__ __launch_bounds__(NTHR) void detect_map_kernel(DetArgs a) {
     // a thread are issued (from clamped rows) before any is used.
     constexpr int NCH = (ROWS + 2) * (SEG / 4), NIT = (NCH + NTHR - 1) / NTHR;
     if (a.vec && x0 + SEG <= a.W) {
-        float4 Dv[NIT], Vv[NIT];
-        uint32_t Mv[NIT];
+        // (a thread's chunks are on the same four columns)
+        static_assert(NTHR % (SEG / 4) == 0, "chunks of a thread share their columns");
+        typename std::conditional<SRC, BgColumns<4>, NoColumns>::type col(a.bg, x0 + 4 * (tid % (SEG / 4)));
+        // difference mode issues every load at once; the source mode's columns
+        // leave registers for BATCH chunks at six waves per SIMD
+        constexpr int BATCH = SRC ? 3 : NIT;
 #pragma unroll
-        for (int j = 0; j < NIT; ++j) {
-            const int i = tid + j * NTHR, ii = i < NCH ? i : 0;
-            const int row = ii / (SEG / 4), ch = ii % (SEG / 4);
-            int y = y0 - 1 + row;
-            y = y < 0 ? 0 : (y >= a.H ? a.H - 1 : y);
-            const int64_t o = (int64_t)y * P + x0 + 4 * ch;
-            Dv[j] = *(const float4 *)(a.diff + o);
-            Vv[j] = *(const float4 *)(a.dvar + o);
-            Mv[j] = *(const uint32_t *)(a.dmask + o);
-        }
+        for (int j0 = 0; j0 < NIT; j0 += BATCH) {
+            float4 Dv[BATCH], Vv[BATCH];
+            uint32_t Mv[BATCH];
 #pragma unroll
-        for (int j = 0; j < NIT; ++j) {
-            const int i = tid + j * NTHR;
-            if (i < NCH) {
-                const int row = i / (SEG / 4), ch = i % (SEG / 4);
-                const int y = y0 - 1 + row;
-                float4 v;
-                if (y < 0 || y >= a.H) {
-                    v = make_float4(-__builtin_inff(), -__builtin_inff(), -__builtin_inff(),
-                                    -__builtin_inff());
-                } else {
-                    float4 D = Dv[j];
-                    const float4 V = Vv[j];
-                    const uint32_t m = Mv[j];
-                    if constexpr (SRC) {
-                        const int x = x0 + 4 * ch;
-                        D.x -= bg_at(a.bg, x, y);
-                        D.y -= bg_at(a.bg, x + 1, y);
-                        D.z -= bg_at(a.bg, x + 2, y);
-                        D.w -= bg_at(a.bg, x + 3, y);
+            for (int j = 0; j < BATCH; ++j) {
+                const int i = tid + (j0 + j) * NTHR, ii = i < NCH ? i : 0;
+                const int row = ii / (SEG / 4), ch = ii % (SEG / 4);
+                int y = y0 - 1 + row;
+                y = y < 0 ? 0 : (y >= a.H ? a.H - 1 : y);
+                const int64_t o = (int64_t)y * P + x0 + 4 * ch;
+                Dv[j] = *(const float4 *)(a.diff + o);
+                Vv[j] = *(const float4 *)(a.dvar + o);
+                Mv[j] = *(const uint32_t *)(a.dmask + o);
+            }
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {
+                const int i = tid + (j0 + j) * NTHR;
+                if (i < NCH) {
+                    const int row = i / (SEG / 4), ch = i % (SEG / 4);
+                    const int y = y0 - 1 + row;
+                    float4 v;
+                    if (y < 0 || y >= a.H) {
+                        v = make_float4(-__builtin_inff(), -__builtin_inff(), -__builtin_inff(),
+                                        -__builtin_inff());
+                    } else {
+                        float4 D = Dv[j];
+                        const float4 V = Vv[j];
+                        const uint32_t m = Mv[j];
+                        if constexpr (SRC) {
+                            float b[4];
+                            col.at(a.bg, y, b);
+                            D.x -= b[0];
+                            D.y -= b[1];
+                            D.z -= b[2];
+                            D.w -= b[3];
+                        }
+                        v = make_float4(snr_of(D.x, V.x, m & 0xffu),
+                                        snr_of(D.y, V.y, (m >> 8) & 0xffu),
+                                        snr_of(D.z, V.z, (m >> 16) & 0xffu),
+                                        snr_of(D.w, V.w, m >> 24));
                     }
-                    v = make_float4(snr_of(D.x, V.x, m & 0xffu),
-                                    snr_of(D.y, V.y, (m >> 8) & 0xffu),
-                                    snr_of(D.z, V.z, (m >> 16) & 0xffu),
-                                    snr_of(D.w, V.w, m >> 24));
+                    *(float4 *)&s[row][4 + 4 * ch] = v;
                 }
-                *(float4 *)&s[row][4 + 4 * ch] = v;
             }
         }
     } else {
@@ -223,13 +239,13 @@ __global__ __launch_bounds__(NTHR) void scan_tiles_kernel(DetArgs a) {
     if (tid == NTHR - 1) a.tile_sum[t] = wbase + inc;
 }
 
+// A wave takes a.group consecutive segments; within one it reads the whole
+// segment's flags at once and, per candidate, 4 window samples a lane at a
+// time.  What bounds it is the chain of dependent loads per candidate, so the
+// segments are dealt thinly (a.group) and loads go out in batches.
 template <bool SRC>
 __global__ __launch_bounds__(NTHR) void detect_emit_kernel(DetArgs a) {
     const int lane = threadIdx.x & 63;
-    // a wave reads the counts of 64 segments at once (one load per lane, most
-    // segments hold no candidate) and visits those with candidates; groups of
-    // 64 segments are strided over all waves
-    const int nw = gridDim.x * (NTHR / 64);
     // the total goes out from the first wave (the sum of every scan tile)
     if (blockIdx.x == 0 && threadIdx.x < 64) {
         int tot = 0;
@@ -237,92 +253,118 @@ __global__ __launch_bounds__(NTHR) void detect_emit_kernel(DetArgs a) {
         for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off);
         if (lane == 0) *a.n_cands = tot;
     }
-    for (int s0 = (blockIdx.x * (NTHR / 64) + (threadIdx.x >> 6)) * 64; s0 < a.nseg; s0 += nw * 64) {
-        const bool has = s0 + lane < a.nseg && a.counts[s0 + lane] != 0;
-        uint64_t segs = __ballot(has);
-        if (!segs) continue;
-        // the 64 segments share one scan tile (STILE is a multiple of 64):
-        // its offset is the sum of the tiles before it
-        int toff = 0;
-        for (int t = lane; t < s0 / STILE; t += 64) toff += a.tile_sum[t];
-        for (int off = 32; off > 0; off >>= 1) toff += __shfl_xor(toff, off);
-        while (segs) {
-            const int seg = s0 + __builtin_ctzll(segs);
-            segs &= segs - 1;
-            int idx = toff + a.local[seg];
-            const int y = seg / a.nsx, x0 = (seg % a.nsx) * SEG;
-            const int64_t orow = (int64_t)y * a.pitch;
-            const int K = 2 * a.r + 1;
-            for (int c0 = 0; c0 < SEG && idx < a.cap; c0 += 64) {
-                const int x = x0 + c0 + lane;
-                const bool isc = x < a.W && (a.det[orow + x] & ARGUS_CAND);
-                uint64_t bal = __ballot(isc);
-                while (bal && idx < a.cap) {
-                    const int l = __builtin_ctzll(bal);
-                    bal &= bal - 1;
-                    const int cx = x0 + c0 + l;
-                    // PSF-weighted flux over unmasked in-image pixels of the window
-                    double q = 0.0, f = 0.0;
-                    for (int t = lane; t < K * K; t += 64) {
-                        int xx = cx + t % K - a.r, yy = y + t / K - a.r;
-                        if (xx < 0 || xx >= a.W || yy < 0 || yy >= a.H) continue;
-                        int64_t o = (int64_t)yy * a.pitch + xx;
-                        float V = a.dvar[o];
-                        if (a.dmask[o] != 0 || !(V > 0.f)) continue;
-                        double p = (double)a.psf[t];
-                        q += p * p / (double)V;
-                        f += p * (double)d_at<SRC>(a, o, xx, yy) / (double)V;
+    const int wave = blockIdx.x * (NTHR / 64) + (threadIdx.x >> 6);
+    const int s0 = wave * a.group, s1 = min(s0 + a.group, a.nseg);
+    int32_t cnt = 0, loc = 0;
+    if (s0 + lane < s1) {
+        cnt = a.counts[s0 + lane];
+        loc = a.local[s0 + lane];
+    }
+    uint64_t segs = __ballot(cnt != 0);
+    if (!segs) return;
+    // the group's segments share one scan tile (STILE is a multiple of it):
+    // its offset is the sum of the tiles before it
+    int toff = 0;
+    for (int t = lane; t < s0 / STILE; t += 64) toff += a.tile_sum[t];
+    for (int off = 32; off > 0; off >>= 1) toff += __shfl_xor(toff, off);
+    const int K = 2 * a.r + 1, KK = K * K;
+    while (segs) {
+        const int sl = __builtin_ctzll(segs), seg = s0 + sl;
+        segs &= segs - 1;
+        int idx = toff + __builtin_amdgcn_readlane(loc, sl);
+        const int y = seg / a.nsx, x0 = (seg % a.nsx) * SEG;
+        const int64_t orow = (int64_t)y * a.pitch;
+        // the flags of this lane's 4 pixels
+        const int xl = x0 + 4 * lane;
+        uint32_t fl = 0;
+        if (a.vec && xl + 3 < a.W) {
+            fl = *(const uint32_t *)(a.det + orow + xl);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (xl + e < a.W) fl |= (uint32_t)a.det[orow + xl + e] << (8 * e);
+        }
+        fl &= 0x01010101u * ARGUS_CAND;
+        uint64_t bal = __ballot(fl != 0);
+        while (bal && idx < a.cap) {
+            const int l = __builtin_ctzll(bal);
+            bal &= bal - 1;
+            uint32_t f4 = (uint32_t)__builtin_amdgcn_readlane((int)fl, l);
+            for (; f4 && idx < a.cap; f4 &= f4 - 1, ++idx) {
+                const int cx = x0 + 4 * l + (__builtin_ctz(f4) >> 3);
+                const float snr = snr_at<SRC>(a, cx, y);
+                // PSF-weighted flux over unmasked in-image pixels of the window
+                double q = 0.0, f = 0.0;
+                for (int t0 = lane; t0 < KK; t0 += 256) {
+                    float V[4], P[4], Dv[4];
+                    bool ok[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int t = min(t0 + 64 * j, KK - 1);
+                        const int xx = cx + t % K - a.r, yy = y + t / K - a.r;
+                        const int xc = min(max(xx, 0), a.W - 1), yc = min(max(yy, 0), a.H - 1);
+                        const int64_t o = (int64_t)yc * a.pitch + xc;
+                        V[j] = a.dvar[o];
+                        P[j] = a.psf[t];
+                        Dv[j] = d_at<SRC>(a, o, xc, yc);
+                        ok[j] = t0 + 64 * j < KK && xx == xc && yy == yc && a.dmask[o] == 0;
                     }
-                    // source centroid: max(D, 0) over the unmasked in-image 3 x 3
-                    double cs = 0.0, cxs = 0.0, cys = 0.0;
-                    if constexpr (SRC) {
-                        if (lane < 9) {
-                            const int u = lane % 3 - 1, v = lane / 3 - 1, xx = cx + u, yy = y + v;
-                            if (xx >= 0 && xx < a.W && yy >= 0 && yy < a.H) {
-                                const int64_t o = (int64_t)yy * a.pitch + xx;
-                                const float V = a.dvar[o];
-                                if (a.dmask[o] == 0 && V > 0.f) {
-                                    const double d = fmax((double)d_at<SRC>(a, o, xx, yy), 0.0);
-                                    cs = d;
-                                    cxs = u * d;
-                                    cys = v * d;
-                                }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (!ok[j] || !(V[j] > 0.f)) continue;
+                        const double p = (double)P[j];
+                        q += p * p / (double)V[j];
+                        f += p * (double)Dv[j] / (double)V[j];
+                    }
+                }
+                // source centroid: max(D, 0) over the unmasked in-image 3 x 3
+                double cs = 0.0, cxs = 0.0, cys = 0.0;
+                if constexpr (SRC) {
+                    if (lane < 9) {
+                        const int u = lane % 3 - 1, v = lane / 3 - 1, xx = cx + u, yy = y + v;
+                        if (xx >= 0 && xx < a.W && yy >= 0 && yy < a.H) {
+                            const int64_t o = (int64_t)yy * a.pitch + xx;
+                            const float V = a.dvar[o];
+                            if (a.dmask[o] == 0 && V > 0.f) {
+                                const double d = fmax((double)d_at<SRC>(a, o, xx, yy), 0.0);
+                                cs = d;
+                                cxs = u * d;
+                                cys = v * d;
                             }
                         }
                     }
-                    for (int off = 32; off > 0; off >>= 1) {
-                        q += __shfl_xor(q, off);
-                        f += __shfl_xor(f, off);
-                        if constexpr (SRC) {
-                            cs += __shfl_xor(cs, off);
-                            cxs += __shfl_xor(cxs, off);
-                            cys += __shfl_xor(cys, off);
-                        }
+                }
+                for (int off = 32; off > 0; off >>= 1) {
+                    q += __shfl_xor(q, off);
+                    f += __shfl_xor(f, off);
+                    if constexpr (SRC) {
+                        cs += __shfl_xor(cs, off);
+                        cxs += __shfl_xor(cxs, off);
+                        cys += __shfl_xor(cys, off);
                     }
-                    if (lane == 0) {
-                        const float fl = q > 0.0 ? (float)(f / q) : __builtin_nanf("");
-                        const float fe = q > 0.0 ? (float)(1.0 / sqrt(q)) : __builtin_nanf("");
-                        if constexpr (SRC) {
-                            argus_source c;
-                            c.x = cx;
-                            c.y = y;
-                            c.xc = cs > 0.0 ? (float)(cx + cxs / cs) : __builtin_nanf("");
-                            c.yc = cs > 0.0 ? (float)(y + cys / cs) : __builtin_nanf("");
-                            c.snr = snr_at<SRC>(a, cx, y);
-                            c.flux = fl;
-                            c.flux_err = fe;
-                            a.srcs[idx] = c;
-                        } else {
-                            argus_candidate c;
-                            c.x = cx;
-                            c.y = y;
-                            c.snr = snr_at<SRC>(a, cx, y);
-                            c.flux = fl;
-                            c.flux_err = fe;
-                            a.cands[idx] = c;
-                        }
+                }
+                if (lane == 0) {
+                    const float fx = q > 0.0 ? (float)(f / q) : __builtin_nanf("");
+                    const float fe = q > 0.0 ? (float)(1.0 / sqrt(q)) : __builtin_nanf("");
+                    if constexpr (SRC) {
+                        argus_source c;
+                        c.x = cx;
+                        c.y = y;
+                        c.xc = cs > 0.0 ? (float)(cx + cxs / cs) : __builtin_nanf("");
+                        c.yc = cs > 0.0 ? (float)(y + cys / cs) : __builtin_nanf("");
+                        c.snr = snr;
+                        c.flux = fx;
+                        c.flux_err = fe;
+                        a.srcs[idx] = c;
+                    } else {
+                        argus_candidate c;
+                        c.x = cx;
+                        c.y = y;
+                        c.snr = snr;
+                        c.flux = fx;
+                        c.flux_err = fe;
+                        a.cands[idx] = c;
                     }
-                    ++idx;
                 }
             }
         }
@@ -367,8 +409,13 @@ int launch_detect_any(argus_ctx *ctx, argus_dims d, const float *diff, const flo
     argus_time_end(ctx, src ? "source_map" : "detect_map");
     argus_time_begin(ctx);
     hipLaunchKernelGGL(scan_tiles_kernel, dim3(a.ntile), dim3(NTHR), 0, ctx->stream, a);
-    // one wave per 64 segments, at most enough to fill the device a few times over
-    const int eblocks = std::max(1, std::min((a.nseg + 255) / 256, 8 * std::max(ctx->n_cu, 1)));
+    // segments per emitting wave: few enough that about 32 waves per CU share
+    // them (a wave works through its candidates one after the other), at most
+    // 64 (one count per lane)
+    a.group = 1;
+    while (a.group < 64 && (int64_t)a.group * 32 * std::max(ctx->n_cu, 1) < a.nseg) a.group *= 2;
+    const int per = a.group * (NTHR / 64);
+    const int eblocks = (a.nseg + per - 1) / per;
     if (src)
         hipLaunchKernelGGL(detect_emit_kernel<true>, dim3(eblocks), dim3(NTHR), 0, ctx->stream, a);
     else
