@@ -289,19 +289,28 @@ int launch_fit(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, cons
     fa.spt = (maxw + SW - 1) / SW;
     // Row chunks: one workgroup runs per CU at a time, so the accumulation
     // takes ceil(workgroups / CUs) rounds of (rows per chunk + 2h halo rows)
-    // steps each.  Take the chunk count (chunks no shorter than 8h) with the
-    // shortest such makespan, which also avoids a last round that leaves
-    // most CUs idle.
+    // steps of about 1 us + 0.4 us per degree (FP64 moments: twice that), and
+    // every chunk's partial moments are written and read again (at about 3 TB/s
+    // together).  Take the chunk count, chunks of 4 rows and up, with the
+    // smallest sum: large frames get a last round that leaves few CUs idle,
+    // small ones many short chunks (256 x 224, degree 1: 94 -> 30 us against
+    // chunks no shorter than 8h rows).
     {
         const int base = fa.RX * fa.RY * fa.spt;
-        const int maxc = maxh / (8 * fa.h) > 1 ? maxh / (8 * fa.h) : 1;
+        const int maxc = maxh / 4 > 1 ? maxh / 4 : 1;
         const int ncu = ctx->n_cu > 0 ? ctx->n_cu : 256;
-        int64_t best = -1;
+        const int D = spec->spatial_degree;
+        const double step_us = (1.0 + 0.4 * D) * (spec->precision == ARGUS_FP64 ? 2.0 : 1.0);
+        const double part_us = 2.0 * 8.0 * 768.0 * argus_npoly(2 * D) / 3e6;
+        double best = -1.0;
         fa.rchunks = 1;
         for (int c = 1; c <= maxc; ++c) {
-            const int64_t rounds = ((int64_t)base * c + ncu - 1) / ncu;
-            const int64_t t = rounds * ((maxh + c - 1) / c + 2 * fa.h);
-            if (best < 0 || t < best) {
+            const int64_t wg = (int64_t)base * c, rounds = (wg + ncu - 1) / ncu;
+            // (halo rows and partials only grow with c)
+            const double least = (double)(rounds * 2 * fa.h) * step_us + (double)wg * part_us;
+            if (best >= 0.0 && least >= best) break;
+            const double t = least + (double)(rounds * ((maxh + c - 1) / c)) * step_us;
+            if (best < 0.0 || t < best) {
                 best = t;
                 fa.rchunks = c;
             }
