@@ -730,5 +730,8 @@ int fit_accum_launch(argus_ctx *ctx, const FitArgs &fa, int D, dim3 grid) {
 
 // One launcher per precision, each in its own translation unit.
 int fit_accum_launch_fp32(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
+// the FP32 fit of degree 1 or 2 on frames at least FIT_WIDE_MIN columns wide
+int fit_accum_launch_wide(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
+constexpr int FIT_WIDE_MIN = 6144;
 int fit_accum_launch_fp64(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
 int fit_accum_launch_bf16x3(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);

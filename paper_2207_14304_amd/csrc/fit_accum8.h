@@ -59,7 +59,7 @@ struct FitLds8 {
     __device__ float *wsx(int b) const { return wsx0 + b * (FitShape<D>::NRA * SW); }
     __device__ double *wxd(int b) const { return wxd0 + b * (FitShape<D>::NA * SW); }
     __device__ double *wsxd(int b) const { return wsxd0 + b * (FitShape<D>::NRA * SW); }
-    __host__ __device__ static size_t bytes(int nwm) {
+    __host__ __device__ static constexpr size_t bytes(int nwm) {
         using S = FitShape<D>;
         size_t w = 2 * INP + 2 * 32 * CKM + 2 * (S::NA + S::NRA) * SW + (TS ? 2 * TSB : 0);
         size_t b = w * 4 + (size_t)2 * (S::NA + S::NRA) * SW * 8 + 4 * 8;
@@ -91,8 +91,9 @@ __device__ __forceinline__ int fit8_strip_steps(int rows) { return fit8_steps(ro
 // to NP planes (from plist8 for 8 waves, plist for 4).  Wave 0 (W0) also
 // stages the fit-set weights (with 8 waves it takes one plane, so that its
 // registers fit the same budget); it returns the number of fit pixels it
-// counted, the others return 0.
-template <int D, int HH, int PREC, int NWC, int NP, bool W0>
+// counted, the others return 0.  WIDE (fit_wide.h): the weights go out as
+// sqrt(w) and sqrt(w) s xt^e, and the pipeline drains one step more.
+template <int D, int HH, int PREC, int NWC, int NP, bool W0, bool WIDE = false>
 __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end, int ry0,
                          int ry1, bool active, int cw) {
     using S = FitShape<D>;
@@ -295,6 +296,16 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
                         }
                         float xp = 1.f;
                         double xpd = 1.0;
+                        if constexpr (WIDE) {
+                            const float q = __builtin_amdgcn_sqrtf(w);
+                            l.wx(buf)[lane] = q;
+                            float t = q * w_s;
+#pragma unroll
+                            for (int e = 0; e < S::NRA; ++e) {
+                                l.wsx(buf)[e * SW + lane] = t * xp;
+                                xp *= xt;
+                            }
+                        } else
 #pragma unroll
                         for (int e = 0; e < S::NA; ++e) {
                             l.wx(buf)[e * SW + lane] = w * xp;
@@ -346,7 +357,7 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
         // count is padded to whole blocks (the MFMA waves count alike)
         // (an odd first row gets one leading step that only keeps the count)
         const int ys0 = ystart & ~1;
-        const int ylast = ys0 + fit8_strip_steps<TS>(yend - ys0) - 1;
+        const int ylast = ys0 + fit8_strip_steps<TS || WIDE>(yend - ys0) - 1;
         for (int yy = ys0; yy <= ylast; yy += U8) {
             step(std::integral_constant<int, 0>{}, yy);
             step(std::integral_constant<int, 1>{}, yy + 1);

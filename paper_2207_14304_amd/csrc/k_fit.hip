@@ -177,7 +177,12 @@ int fit_launch_d(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, Fi
     switch (spec->precision) {
         case ARGUS_FP64: rc = fit_accum_launch_fp64(ctx, fa, D, grid); break;
         case ARGUS_BF16X3: rc = fit_accum_launch_bf16x3(ctx, fa, D, grid); break;
-        default: rc = fit_accum_launch_fp32(ctx, fa, D, grid); break;
+        default:
+            if (D >= 1 && d.width >= FIT_WIDE_MIN)
+                rc = fit_accum_launch_wide(ctx, fa, D, grid);
+            else
+                rc = fit_accum_launch_fp32(ctx, fa, D, grid);
+            break;
     }
     if (rc) return rc;
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
