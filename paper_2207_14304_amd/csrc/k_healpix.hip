@@ -42,10 +42,7 @@ struct HpArgs {
     int W, H, nside, m;
 };
 
-constexpr int BS = 32;                 // pixels of a block's side
-constexpr int ND = 2 * BS - 1;         // its diagonals
 constexpr int BOX = 2250;              // frame pixels that the LDS box holds
-constexpr int NK = BS * BS / 256;      // pixels of a thread
 
 // 1 / v for a normal v: the hardware estimate and two Newton steps
 __device__ __forceinline__ double recip(double v) {
@@ -54,13 +51,20 @@ __device__ __forceinline__ double recip(double v) {
     return fma(fma(-v, r, 1.0), r, r);
 }
 
+// BS x BS pixels a workgroup.  BOXED: neighbours from the box in LDS, a wave on
+// rows of the block (whole-line stores); else from the frame, a wave on 8 x 8
+// patches (whose neighbours lie on the fewest lines).
+template <int BS, bool BOXED>
 __global__ __launch_bounds__(256, 7) void healpix_resample_kernel(HpArgs a) {
+    constexpr int ND = 2 * BS - 1;             // diagonals of a block
+    constexpr int NK = BS * BS / 256;          // pixels of a thread
+    constexpr int CAP = BOXED ? BOX : 1;
     __shared__ double sz[ND], sc[ND], si[ND];  // per a + b: z, cos dec, 1 / sigma
     __shared__ double sx[ND];                  // per a - b: longitude from phi_c
     __shared__ double smid[3];                 // the middle's longitude - ra0, its sin and cos
     __shared__ int sbox[4];                    // -xmin, -ymin, xmax, ymax of the neighbours (maxima)
-    __shared__ float2 bv[BOX];                 // the box: value, variance
-    __shared__ uint8_t bm[BOX];                // and mask
+    __shared__ float2 bv[CAP];                 // the box: value, variance
+    __shared__ uint8_t bm[CAP];                // and mask
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // blocks in raster order of their segments, each XCD a contiguous run: the
     // boxes of neighbouring blocks overlap, and share an L2 this way
@@ -114,12 +118,16 @@ __global__ __launch_bounds__(256, 7) void healpix_resample_kernel(HpArgs a) {
     const double r2d = 180.0 / PI;
     const double ax = r2d * a.w.cdi[0], bx = r2d * a.w.cdi[1], ay = r2d * a.w.cdi[2],
                  by = r2d * a.w.cdi[3];
-    const int pl = lane & (BS - 1), p = p0 + pl;
+    // column and row of this thread's pixel k
+    auto col = [&](int k) { return BOXED ? tid & (BS - 1) : 8 * ((wv + 4 * k) % (BS / 8)) + (lane & 7); };
+    auto row = [&](int k) {
+        return BOXED ? tid / BS + 256 / BS * k : 8 * ((wv + 4 * k) / (BS / 8)) + (lane >> 3);
+    };
     double X[NK], Y[NK];
     int ext[4] = {-(1 << 30), -(1 << 30), -(1 << 30), -(1 << 30)};
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int ql = 2 * (wv + 4 * k) + (lane >> 5);
+        const int pl = col(k), ql = row(k), p = p0 + pl;
         const double z = sz[pl + ql], cd = sc[pl + ql];
         const double d = fma(sx[pl - ql + BS - 1], si[pl + ql], off);
         double sd, cs;
@@ -148,34 +156,40 @@ __global__ __launch_bounds__(256, 7) void healpix_resample_kernel(HpArgs a) {
             ext[3] = max(ext[3], min(y0 + 1, a.H - 1));
         }
     }
+    int bx0 = 0, by0 = 0, bs = 0;
+    bool boxed = false;
+    if constexpr (BOXED) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        for (int o = 32; o > 0; o >>= 1) ext[e] = max(ext[e], __shfl_xor(ext[e], o));
-        if (lane == 0) atomicMax(&sbox[e], ext[e]);
-    }
-    __syncthreads();
-    const int bx0 = -sbox[0], by0 = -sbox[1], bw = sbox[2] - bx0 + 1, bh = sbox[3] - by0 + 1;
-    const int bs = bw | 1;                 // odd LDS row stride
-    // (a frame of a much finer scale than the segment does not fit: its
-    // neighbours are gathered from the frame)
-    const bool boxed = bw > 0 && bw <= 64 && bh <= BOX && bs * bh <= BOX;
-    if (boxed) {
-        const int xl = bx0 + min(lane, bw - 1);
+        for (int e = 0; e < 4; ++e) {
+            for (int o = 32; o > 0; o >>= 1) ext[e] = max(ext[e], __shfl_xor(ext[e], o));
+            if (lane == 0) atomicMax(&sbox[e], ext[e]);
+        }
+        __syncthreads();
+        bx0 = -sbox[0];
+        by0 = -sbox[1];
+        const int bw = sbox[2] - bx0 + 1, bh = sbox[3] - by0 + 1;
+        bs = bw | 1;                           // odd LDS row stride
+        // (a box may not fit after all, as where the pixels are sheared near the
+        // poles: its block gathers from the frame)
+        boxed = bw > 0 && bw <= 64 && bh <= BOX && bs * bh <= BOX;
+        if (boxed) {
+            const int xl = bx0 + min(lane, bw - 1);
 #pragma unroll 4
-        for (int r = wv; r < bh; r += 4) {
-            const int64_t o = (int64_t)(by0 + r) * a.pitch + xl;
-            const float2 v = make_float2(a.cal[o], a.var[o]);
-            const uint8_t m = a.mask[o];
-            if (lane < bw) {
-                bv[r * bs + lane] = v;
-                bm[r * bs + lane] = m;
+            for (int r = wv; r < bh; r += 4) {
+                const int64_t o = (int64_t)(by0 + r) * a.pitch + xl;
+                const float2 v = make_float2(a.cal[o], a.var[o]);
+                const uint8_t m = a.mask[o];
+                if (lane < bw) {
+                    bv[r * bs + lane] = v;
+                    bm[r * bs + lane] = m;
+                }
             }
         }
+        __syncthreads();
     }
-    __syncthreads();
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int q = q0 + 2 * (wv + 4 * k) + (lane >> 5);
+        const int p = p0 + col(k), q = q0 + row(k);
         if (p >= a.m || q >= a.m) continue;
         float val = 0.f, vv = 0.f;
         uint8_t msk = ARGUS_NODATA;
@@ -227,10 +241,24 @@ int launch_resample_healpix(argus_ctx *ctx, argus_dims d, const float *cal, cons
     a.cal = cal; a.var = var; a.mask = mask; a.tiles = tiles;
     a.out = out; a.outv = out_var; a.outm = out_mask;
     a.pitch = d.pitch; a.W = d.width; a.H = d.height; a.nside = nside; a.m = m;
-    const int nx = (m + BS - 1) / BS;
+    // side of a segment pixel in frame pixels, and the block whose box fits (a
+    // square turned by 45 degrees): 32 x 32 up to equal scales (full frame, 600^2
+    // pixels: 519 us; 16 x 16 takes 980), 16 x 16 up to twice the frame's
+    // (300^2: 322 us; no box 438, one pixel a thread in rows 505), else no box
+    const double seg = sqrt(4.0 * PI / 12.0) / ((double)nside * m) * (180.0 / PI);
+    const double ratio = seg / sqrt(fabs(a.w.cd[0] * a.w.cd[3] - a.w.cd[1] * a.w.cd[2]));
+    auto fits = [&](int bs) {
+        const double side = bs * ratio * 1.41421356 + 2.0;
+        return side * side <= (double)BOX;
+    };
     argus_time_begin(ctx);
-    hipLaunchKernelGGL(healpix_resample_kernel, dim3(nx * nx, n_tiles),
-                       dim3(256), 0, ctx->stream, a);
+    auto launch = [&](auto kernel, int bs) {
+        const int nx = (m + bs - 1) / bs;
+        hipLaunchKernelGGL(kernel, dim3(nx * nx, n_tiles), dim3(256), 0, ctx->stream, a);
+    };
+    if (fits(32)) launch(healpix_resample_kernel<32, true>, 32);
+    else if (fits(16)) launch(healpix_resample_kernel<16, true>, 16);
+    else launch(healpix_resample_kernel<32, false>, 32);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     argus_time_end(ctx, "healpix_resample");
     return ARGUS_OK;

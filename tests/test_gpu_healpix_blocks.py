@@ -1,6 +1,7 @@
 """Segment resampling where its 32 x 32 blocks and short series meet their
 limits, against the oracle (the bars of the resampling parity test): segment
-sides one under, at and over a block, blocks that the frame only touches,
+sides one under, at and over a block, each block size (segments as fine as the
+frame, half as fine, coarser), blocks that the frame only touches,
 tiles at a pole and wide-angle tiles (offsets beyond the series), the mixed
 tiles on the polar cap's edge, a frame much finer than the segment (its box
 does not fit) and frames one pixel wide or high."""
@@ -17,6 +18,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("W,H,ra0,dec0,rot,scale,nside,m", [
     (60, 50, 83.6, 22.0, 0.3, 1.38, 256, 31),
+    (900, 700, 83.6, -40.2, 0.4, 1.38, 256, 301),
+    (900, 700, 83.6, 70.0, 1.1, 1.38, 256, 601),
     (300, 260, 83.6, -22.0, 0.3, 30.0, 256, 32),
     (300, 260, 211.0, 41.8, 0.8, 25.0, 256, 33),
     (500, 400, 45.3, 89.93, 0.2, 5.0, 256, 160),
