@@ -1,0 +1,101 @@
+"""The matched-filter coadd on matrix instructions (half-widths up to 8) at the
+edges of its tiles, against the oracle: every half-width, frames smaller than a
+tile and one pixel over it, one and eight images, unaligned planes and pitches,
+and tiles with infinite, huge and tiny values, which must reach exactly the
+outputs whose PSF window holds them.  Bars of the matched coadd's parity test
+(Var relative 1e-5, SNR 1e-4 absolute plus 1e-6 relative)."""
+import numpy as np
+import pytest
+
+from oracle import matched
+from paper_2207_14304_amd import argus, synth
+from gpu_util import dev, host, empty, padded
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(ctx, frames, psfs, r, scales, pad=0, shift=0):
+    import torch
+    H, W = frames[0][0].shape
+    d = [[dev(p) for p in f] for f in frames]
+    if pad:
+        d = [[padded(t, pad)[:, shift:] if shift else padded(t, pad) for t in f] for f in d]
+    out = [empty((H, W), torch.float32) if not pad else padded(empty((H, W), torch.float32), pad)
+           for _ in range(3)]
+    if shift:
+        out = [o[:, shift:] for o in out]
+    ctx.coadd_matched([f[0] for f in d], [f[1] for f in d], [f[2] for f in d],
+                      dev(psfs.astype(np.float32)), r, *out, scales=scales)
+    return [host(o) for o in out]
+
+
+def _frames(W, H, n, seed):
+    rng = np.random.default_rng(seed)
+    out = []
+    for _ in range(n):
+        c = rng.normal(5.0, 30.0, (H, W)).astype(np.float32)
+        v = rng.uniform(500.0, 1500.0, (H, W)).astype(np.float32)
+        m = (rng.random((H, W)) < 0.01).astype(np.uint8)
+        c[H // 2, W // 2] += 3000.0
+        out.append((c, v, m))
+    return out
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = argus.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("W,H,r,n,pad,shift", [
+    (64, 32, 1, 1, 0, 0), (65, 33, 2, 2, 0, 0), (200, 70, 3, 3, 3, 0), (63, 31, 4, 8, 0, 0),
+    (130, 97, 5, 2, 5, 1), (192, 64, 6, 2, 0, 0), (257, 129, 7, 3, 4, 0), (300, 65, 8, 4, 0, 0),
+    (5, 3, 8, 2, 0, 0)])
+def test_tile_edges(ctx, W, H, r, n, pad, shift):
+    fr = _frames(W + shift, H, n, W + r)
+    psfs = np.stack([synth.psf_image(r, 1.6 + 0.2 * j) for j in range(n)]).astype(np.float32)
+    scales = [1.0 + 0.05 * j for j in range(n)]
+    g = _run(ctx, fr, psfs, r, scales, pad, shift)
+    fr = [tuple(p[:, shift:] for p in f) for f in fr]
+    F = [float(np.float32(s)) for s in scales]
+    S, V, N = matched.matched_coadd([f[0] for f in fr], [f[1] for f in fr], [f[2] for f in fr],
+                                    [None] * n, [p.astype(np.float64) for p in psfs], F)
+    pos = V > 0
+    assert np.array_equal(g[1] > 0, pos)
+    assert np.abs(g[1][pos] / V[pos] - 1).max() <= 1e-5
+    assert (np.abs(g[2] - N) - 1e-6 * np.abs(N)).max() <= 1e-4
+
+
+@pytest.mark.parametrize("kind", ["inf", "huge", "tiny"])
+def test_strange_values_stay_in_their_window(ctx, kind):
+    W, H, r = 150, 80, 7
+    fr = _frames(W, H, 2, 9)
+    c, v, m = fr[1]
+    m[20, 70] = 0
+    at = (20, 70)
+    if kind == "inf":
+        c[at] = np.inf
+    elif kind == "huge":
+        c[at], v[at] = 3e38, 1e-3                    # M / V overflows
+    else:
+        v[at] = np.float32(2e37)                     # 1 / V = 5e-38
+    psfs = np.stack([synth.psf_image(r, 2.0)] * 2).astype(np.float32)
+    S, V, N = _run(ctx, fr, psfs, r, [1.0, 1.0])
+    win = np.zeros((H, W), bool)
+    if kind != "tiny":
+        win[at[0] - r:at[0] + r + 1, at[1] - r:at[1] + r + 1] = True
+    assert np.array_equal(~np.isfinite(S), win)
+    assert np.all(np.isfinite(V))
+    ok = ~win
+    zero = [(np.where(np.isfinite(f[0]) & (np.abs(f[0]) < 1e30), f[0], 0), f[1], f[2]) for f in fr]
+    if kind != "tiny":
+        zero[1][2][at] = 1
+    oS, oV, oN = matched.matched_coadd([f[0] for f in zero], [f[1] for f in zero],
+                                       [f[2] for f in zero], [None] * 2,
+                                       [p.astype(np.float64) for p in psfs], [1.0, 1.0])
+    assert (np.abs(N - oN) - 1e-6 * np.abs(oN))[ok].max() <= 1e-4
+    assert np.abs(V[ok] / oV[ok] - 1).max() <= 1e-5
