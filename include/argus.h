@@ -414,9 +414,9 @@ int argus_zogy(argus_ctx *ctx, argus_dims dims, const float *new_img, const uint
 
 /* ---- batched cutouts (per-segment subtraction, Transient Alerts; Table 2) --
  * Many target cutouts from many cameras' frames, each fit with its own
- * spatially constant kernel and differenced, in ONE persistent launch that
- * workgroups drain from a work queue (largest cutouts first), captured in a
- * HIP graph.  Each cutout is treated as a standalone image of side L: its
+ * spatially constant kernel and differenced: fit tasks that a persistent grid
+ * drains from a work queue (largest cutouts first), solves, subtraction and
+ * detection tiles, captured as one HIP graph.  Each cutout is treated as a standalone image of side L: its
  * fit set, edges and footprints stay inside the cutout (the same result as
  * argus_fit_kernel / argus_subtract / argus_detect on an L x L copy).
  * Spec: spatial_degree = bg_degree = 0, mode GLOBAL, precision FP32 or
@@ -447,7 +447,8 @@ typedef struct argus_batch argus_batch;
 
 /* Validate the HOST cutout table against n_frames frames of the given sizes
  * (widths/heights: HOST arrays), order the work, upload it and size the
- * workspace.  Allocates; call outside stream capture. */
+ * workspace (the plan's own: up to 210 MB of partial sums, a kernel stamp per
+ * cutout, 12 bytes per 1024 output pixels).  Allocates; call outside stream capture. */
 int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec,
                      const argus_cutout *cutouts, int n_cutouts,
                      const int32_t *frame_widths, const int32_t *frame_heights,
@@ -455,7 +456,7 @@ int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec,
 /* Run the batch on the frames (HOST array of n_frames descriptors).  The
  * first run times every candidate tile shape and workgroup count on these
  * inputs (the autotuner), keeps the fastest, and captures the queue reset
- * and the persistent kernel in a HIP graph; later runs with the same frame
+ * and the kernels in a HIP graph; later runs with the same frame
  * and output pointers replay the graph. */
 int argus_batch_run(argus_ctx *ctx, argus_batch *batch, const argus_frame *frames,
                     float threshold, float *diff, float *diff_var, uint8_t *diff_mask,
@@ -471,7 +472,7 @@ int argus_batch_info(const argus_batch *batch, int *choice, float *ms, int *n_ca
 int argus_batch_tuning(const argus_batch *batch, float *cand_ms, int capacity, int *n_candidates,
                        int *from_cache);
 /* Shape of autotuner candidate `index`: subtraction tile height in rows and
- * workgroups per compute unit of the persistent launch.  ARGUS_EINVAL for an
+ * workgroups per compute unit of the persistent fit launch.  ARGUS_EINVAL for an
  * index outside the candidate list. */
 int argus_batch_candidate(int index, int *tile_rows, int *wg_per_cu);
 void argus_batch_destroy(argus_batch *batch);

@@ -14,9 +14,7 @@
 // a filter needs.
 //
 // The operand tables are k-major (c[k][p]) so that a lane's operands of
-// four consecutive MFMA steps are one 16-byte LDS read; the per-row sums
-// take the pixels in a different order than fit_wave, otherwise the
-// moments, products and FP64 flushes are those of fit_wave.
+// four consecutive MFMA steps are one 16-byte LDS read.
 #pragma once
 #include <type_traits>
 #include "fit_accum.h"

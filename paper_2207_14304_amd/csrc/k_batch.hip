@@ -20,7 +20,8 @@
 // One workgroup per cutout for all four steps, the form before, took 22.0 ms
 // for 1500 cutouts (93 Mpixel, 15x15, FP64 moments) at two waves per SIMD,
 // with the 512-pixel cutouts alone setting the time of small batches; this
-// form takes @BATCH_MS@.
+// form takes 6.6 ms (fit 4.4, subtract 1.6, detect 0.33, solve 0.05); 40 cutouts,
+// 14.9 ms before, take 0.25.
 #include <stdio.h>
 #include <string.h>
 
@@ -81,10 +82,10 @@ struct argus_batch {
 namespace {
 
 using argus_fit::SW;
-using argus_fit::uload;
 
 constexpr int CHUNK = 128;     // most output rows of a fit task: its 2h extra input rows are
-                               // then about a tenth of a task, and 40 cutouts fill the chip
+                               // then about a tenth of its row filters, and 40 cutouts
+                               // (150 tasks) still spread over the chip
 constexpr int PST = 801;       // doubles of a partial: 3 blocks of 16x16, 32 rhs, fit pixels
 constexpr int ROUND = 32768;   // partials of a round (210 MB)
 constexpr int BW = 64;         // tile width of subtraction and detection
@@ -135,9 +136,11 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // right-hand side.
 // The filters run tap by tap without pairing the symmetric taps: small
 // cutouts' systems amplify FP32 rounding, so its order is kept.
-// What bounds it: FP64 MFMA (48 instructions of 64 cycles per 64 pixels) and
-// the filters' FMAs ((planes + basis functions) (2h+1) per pixel) are about
-// equal and overlap in part.
+// What bounds it: per 64 pixels a compute unit's four SIMDs issue 48 FP64 MFMA
+// of 64 cycles and about 4600 cycles of VALU (2600 of them the filters' (planes
+// + basis functions) (2h+1) FMAs); the two hardly overlap and fill 90% of the
+// kernel's time.  Chunks of 96, 192 and 256 rows: 1.02, 0.98 and 0.97 of the
+// time of 128 at 1500 cutouts, 1.14, 1.20 and 1.46 at 40.
 template <int HH, int PREC>
 struct FitLds {
     static constexpr int IN = SW + 2 * HH, INP = (IN + 3) & ~3, CKM = SW + 4;
@@ -148,6 +151,21 @@ struct FitLds {
     uint64_t bits[2][2][2];        // flagged input pixels
     double rhs[4][32];
     int count[2];
+};
+
+// One filter's coefficients in scalar registers, loaded as a whole (rows of
+// the tables are 128 bytes).
+typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+template <int K>
+struct Taps {
+    floatx16 a;
+    floatx8 b;
+    __device__ __forceinline__ void load(const float *p) {
+        a = *(const __attribute__((address_space(4))) floatx16 *)p;
+        if constexpr (K > 16) b = *(const __attribute__((address_space(4))) floatx8 *)(p + 16);
+    }
+    __device__ __forceinline__ float get(int i) const { return i < 16 ? a[i & 15] : b[i & 7]; }
 };
 
 template <int HH, int PREC>
@@ -179,7 +197,7 @@ __device__ void fit_conv(const BatchArgs &a, FitLds<HH, PREC> &l, int cw, int la
         if (t < steps) {
             // (the tables' address is hidden from the loop, so their values
             // are read where they are used instead of being kept, and spilled,
-            // across it)
+            // across it; reading a filter ahead costs more moves than it hides)
             const BasisTables *tab = a.tab;
             asm volatile("" : "+s"(tab));
             {
@@ -193,13 +211,13 @@ __device__ void fit_conv(const BatchArgs &a, FitLds<HH, PREC> &l, int cw, int la
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
                     if (pl[j] >= 0) {
-                        const float *f = &tab->rowf[pl[j]][0];
+                        Taps<K> f;
+                        f.load(&tab->rowf[pl[j]][0]);
                         float a0 = 0.f, a1 = 0.f;
 #pragma unroll
                         for (int uu = 0; uu < K; ++uu) {
-                            const float k = uload(f + uu);
-                            a0 += k * w0[uu];
-                            a1 += k * w1[uu];
+                            a0 += f.get(uu) * w0[uu];
+                            a1 += f.get(uu) * w1[uu];
                         }
                         rw[j][K - 1 + 2 * u] = a0;
                         rw[j][K + 2 * u] = a1;
@@ -213,13 +231,13 @@ __device__ void fit_conv(const BatchArgs &a, FitLds<HH, PREC> &l, int cw, int la
 #pragma unroll
                     for (int q = 0; q < 7; ++q) {
                         if (q < nk[j]) {
-                            const float *f = &tab->colf[k0[j] + q][0];
+                            Taps<K> f;
+                            f.load(&tab->colf[k0[j] + q][0]);
                             float a0 = 0.f, a1 = 0.f;
 #pragma unroll
                             for (int jj = 0; jj < K; ++jj) {
-                                const float k = uload(f + 2 * HH - jj);
-                                a0 += k * rw[j][2 * u + jj];
-                                a1 += k * rw[j][2 * u + 1 + jj];
+                                a0 += f.get(2 * HH - jj) * rw[j][2 * u + jj];
+                                a1 += f.get(2 * HH - jj) * rw[j][2 * u + 1 + jj];
                             }
                             c0[(k0[j] + q) * L::CKM] = a0;
                             c1[(k0[j] + q) * L::CKM] = a1;

@@ -17,7 +17,6 @@
 using argus_fit::FitArgs;
 using argus_fit::FitShape;
 using argus_fit::SW;
-using argus_fit::NTHR;
 
 namespace {
 

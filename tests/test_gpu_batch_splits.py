@@ -1,0 +1,114 @@
+"""Where a batch cutout is cut into work: 64-column strips of at most 128 output
+rows in the fit, 64-wide tiles in subtraction and detection, rounds of at most
+32768 partial sums.  Sides one below, at and above those edges, for the
+smallest, a middle and the largest half width, against the FP64 oracle on each
+cutout as a standalone image; cutouts too small for the system; and a batch of
+several rounds, whose equal cutouts give equal bits.
+
+Bars: masks, fit counts, statuses, detections exact; chi^2 relative 1e-5
+(FP32 difference and weights, about 1e-6 of a sigma per pixel at S/N up to
+1e3); difference RMS 1e-3 sigma and maximum 1e-2 sigma: the basis convolutions
+are FP32 (6e-8 relative), the solved kernel of a few thousand pixels amplifies
+them by at most about 1e3 in the stamp, and a pixel is at most 1e2 sigma over
+most of a cutout."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2207_14304_amd import argus, synth
+from gpu_util import dev, host, empty
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = argus.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def frame():
+    W, H = 560, 520
+    fp = synth.make_pair(W, H, 500, 71, 1.8, 2.4, n_transients=5)
+    cs, vs, ms = oracle.calibrate(fp.sci_raw, fp.dark, fp.flat, fp.bpm)
+    cr, vr, mr = oracle.calibrate(fp.ref_raw[0], fp.dark, fp.flat, fp.bpm)
+    rng = np.random.default_rng(5)
+    mr[rng.random(mr.shape) < 2e-4] |= oracle.SAT
+    ms[rng.random(ms.shape) < 5e-4] |= oracle.BAD
+    f = lambda a: a.astype(np.float32)
+    return f(cr), f(vr), mr, f(cs), f(vs), ms
+
+
+def _run(ctx, frame, x0, y0, side, h, precision=argus.FP64):
+    import torch
+    H, W = frame[0].shape
+    spec = argus.make_spec(half_width=h, precision=precision)
+    b = argus.Batch(ctx, spec, [0] * len(side), x0, y0, side, [W], [H])
+    o = dict(diff=empty(b.arena, torch.float32), var=empty(b.arena, torch.float32),
+             mask=empty(b.arena, torch.uint8), det=empty(b.arena, torch.uint8),
+             coeffs=empty((b.n, 32), torch.float64), chi2=empty(b.n, torch.float64),
+             n_fit=empty(b.n, torch.int64), status=empty(b.n, torch.int32),
+             n_cands=empty(b.n, torch.int32))
+    ctx.batch_run(b, [tuple(dev(p) for p in frame)], 5.0, *o.values())
+    torch.cuda.synchronize()
+    return b, o
+
+
+@pytest.mark.parametrize("precision", [argus.FP64, argus.FP32])
+@pytest.mark.parametrize("h,sides", [
+    (4, [71, 72, 73, 136, 137]),
+    (7, [63, 65, 77, 78, 79, 142, 143, 271]),
+    (10, [83, 84, 85, 149, 512]),
+])
+def test_sides_at_the_edges(ctx, frame, h, sides, precision):
+    H, W = frame[0].shape
+    side = np.array(sides)
+    x0, y0 = np.minimum(13 * np.arange(len(side)) + 2, W - side), np.minimum(5, H - side)
+    b, o = _run(ctx, frame, x0, y0, side, h, precision)
+    o = {k: host(v) for k, v in o.items()}
+    spec = oracle.KernelSpec(half_width=h)
+    for i, L in enumerate(sides):
+        planes = [p[y0[i]:y0[i] + L, x0[i]:x0[i] + L] for p in frame]
+        co, st, nf = oracle.fit_kernel(*planes, spec)
+        stamps, bg = oracle.expand_kernel(co, spec)
+        D, V, dm, c2, _ = oracle.subtract(stamps, bg, *planes, spec)
+        snr, det, cands = oracle.detect(D, V, dm, 5.0, np.ones((1, 1)))
+        s = slice(b.offsets[i], b.offsets[i] + L * L)
+        assert o["status"][i] == st[0] == 0 and o["n_fit"][i] == nf, L
+        assert np.array_equal(o["mask"][s].reshape(L, L), dm), L
+        ok = dm == 0
+        err = (o["diff"][s].reshape(L, L)[ok] - D[ok]) / np.sqrt(V[ok])
+        assert np.sqrt(np.mean(err ** 2)) <= 1e-3 and np.abs(err).max() <= 1e-2, (L, np.abs(err).max())
+        assert abs(o["chi2"][i] / c2[0] - 1) <= 1e-5, L
+        near = np.abs(snr - 5.0) <= 1e-2
+        assert np.array_equal(o["det"][s].reshape(L, L)[~near], det[~near]), L
+        assert near.any() or o["n_cands"][i] == len(cands), L
+
+
+@pytest.mark.parametrize("h,side", [(4, 10), (7, 16), (7, 19), (10, 22)])
+def test_too_few_pixels(ctx, frame, h, side):
+    """The smallest cutouts have fewer fit pixels than unknowns."""
+    b, o = _run(ctx, frame, [3], [4], [side], h)
+    assert host(o["status"])[0] == argus.ETOOFEW and np.isnan(host(o["coeffs"])[0]).all()
+    m = host(o["mask"])[:side * side]
+    assert host(o["n_fit"])[0] <= (side - 2 * h) ** 2 and host(o["n_cands"])[0] == 0
+    assert np.isnan(host(o["diff"])[:side * side][m == 0]).all()
+
+
+def test_several_rounds(ctx, frame):
+    """1100 cutouts of 512 x 512 pixels take 35200 partial sums, two rounds."""
+    import torch
+    n, L = 1100, 512
+    b, o = _run(ctx, frame, np.full(n, 20), np.full(n, 6), np.full(n, L), 7)
+    for k in ("diff", "var", "mask", "det"):
+        v = o[k].view(torch.uint8) if o[k].dtype != torch.uint8 else o[k]
+        v = v[:v.numel() // b.arena * n * L * L].view(n, -1)
+        assert all(torch.equal(v[0], v[i]) for i in (1, 511, 1023, 1024, 1025, 1099)), k
+    for k in ("coeffs", "chi2", "n_fit", "status", "n_cands"):
+        v = o[k]
+        assert bool((v == v[:1]).all()), k
