@@ -14,6 +14,7 @@
 // convolution with the weights transposed in (in, out) and flipped in taps.
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "internal.h"
@@ -49,11 +50,9 @@ __device__ __forceinline__ float bf2f(bf16 x) { return (float)x; }
 
 // ---------------------------------------------------------------------------
 // Convolution: two workgroups per stamp, one per band of output rows (0..15
-// and 16..30: 31 and 30 output tiles of 16 raster pixels x 32 channels
-// spread over the waves); K = 9 * CIN (padded to 32) per tile.  A band holds
-// its 18 input rows (with the halo) in LDS, so four workgroups fit a CU.  The
+// and 16..30).  A band holds its 18 input rows (with the halo) in LDS.  The
 // weight fragments of every K step stay in registers (loaded once from global
-// memory), so the tile loop reads only the activations from LDS.
+// memory), so the loops read only the activations from LDS.
 // MODE 0: z + bias, ReLU.  MODE 1: gate by (g > 0) (backward data).
 struct ConvArgs {
     const bf16 *in, *w, *gate;
@@ -64,208 +63,242 @@ struct ConvArgs {
     int npx, n;                                 // pixels per stamp (961), stamps
 };
 
-template <int CIN>
-struct ConvShape {
-    static constexpr int KP = ((9 * CIN + 31) / 32) * 32, KS = KP / 32, PW = 33;
-    static constexpr int BAND = 16, NBAND = 2;          // output rows per band, bands per stamp
-    static constexpr int AROWS = BAND + 2;              // input rows y0 - 1 .. y0 + BAND
-    static constexpr int ACT = (AROWS * PW * CIN + 7) & ~7;
-};
+constexpr int BAND = 16, NBAND = 2;             // output rows per band, bands per stamp
+constexpr int AROWS = BAND + 2;                 // input rows y0 - 1 .. y0 + BAND
+constexpr int CT = 256, CNW = CT / 64;          // 4-wave workgroups
+constexpr int CPW = 2;                          // resident 32-channel workgroups per CU
 
-// 4-wave workgroups, four per CU (LDS and registers)
-template <int MODE>
-constexpr int conv_threads() { return 256; }
-
-template <int CIN, int MODE>
-__global__ __launch_bounds__(conv_threads<MODE>(), 4) void cnn_conv_kernel(ConvArgs a) {
-    constexpr int CTM = conv_threads<MODE>();
-    using CS = ConvShape<CIN>;
-    constexpr int KP = CS::KP, KS = CS::KS, W = 31, PW = CS::PW;
-    extern __shared__ __align__(16) bf16 sm[];
-    bf16 *act = sm;                             // [18][33][CIN]: rows y0 - 1 .. y0 + 16, zero border
+// The first layer (2 input channels, K = 18 padded to 32): 31 and 30 tiles of
+// 16 raster pixels x 32 channels per band, spread over the waves.
+__global__ __launch_bounds__(CT, 4) void cnn_conv2_kernel(ConvArgs a) {
+    constexpr int KP = 32, W = 31, PW = 33, ACT = (AROWS * PW * 2 + 7) & ~7;
+    __shared__ __align__(16) bf16 act[ACT];     // [18][33][2]: rows y0 - 1 .. y0 + 16, zero border
     // the valid stamps come first in the grid (compacted order); the rest of
     // the workgroups leave at once
-    if ((int)blockIdx.x >= *a.nvalid * CS::NBAND) return;
-    const int s = a.order[blockIdx.x / CS::NBAND], tid = threadIdx.x;
-    const int y0 = (blockIdx.x % CS::NBAND) * CS::BAND;          // first output row of the band
-    const int p0 = y0 * W, p1 = min(a.npx, p0 + CS::BAND * W);   // its pixels
+    if ((int)blockIdx.x >= *a.nvalid * NBAND) return;
+    const int s = a.order[blockIdx.x / NBAND], tid = threadIdx.x;
+    const int y0 = (blockIdx.x % NBAND) * BAND;                  // first output row of the band
+    const int p0 = y0 * W, p1 = min(a.npx, p0 + BAND * W);       // its pixels
     const int lane = tid & 63, wave = tid >> 6, col = lane & 15, g = lane >> 4;
-    // B fragments: output channels 2 col (B0) and 2 col + 1 (B1), k = ks*32 +
-    // 8g .. +7, so a lane's two results of a pixel are adjacent channels
-    bf16x8 B0[KS], B1[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        B0[ks] = *(const bf16x8 *)&a.w[(2 * col) * KP + ks * 32 + 8 * g];
-        B1[ks] = *(const bf16x8 *)&a.w[(2 * col + 1) * KP + ks * 32 + 8 * g];
-    }
-    for (int i = tid; i < CS::ACT / 8; i += CTM) ((uint4 *)act)[i] = make_uint4(0u, 0u, 0u, 0u);
+    // B fragments: output channels 2 col (B0) and 2 col + 1 (B1), k = 8g ..
+    // +7, so a lane's two results of a pixel are adjacent channels
+    const bf16x8 B0 = *(const bf16x8 *)&a.w[(2 * col) * KP + 8 * g];
+    const bf16x8 B1 = *(const bf16x8 *)&a.w[(2 * col + 1) * KP + 8 * g];
+    for (int i = tid; i < ACT / 8; i += CT) ((uint4 *)act)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     // the input rows of the band that lie in the stamp: pixels q0 .. q1 - 1,
-    // LDS row y - y0 + 1
-    const int q0 = max(y0 - 1, 0) * W, q1 = min(a.npx, (y0 + CS::BAND + 1) * W);
-    const bf16 *src = a.in + (size_t)s * a.npx * CIN;
-    if constexpr (CIN % 8 == 0) {
-        // 16-byte pieces (8 channels of a pixel), eight loads in flight per
-        // thread before their LDS stores
-        constexpr int C8 = CIN / 8, U = 8;
-        const int n8 = (q1 - q0) * C8;
-        const uint4 *src4 = (const uint4 *)(src + (size_t)q0 * CIN);
-        for (int i0 = tid; i0 < n8; i0 += CTM * U) {
-            uint4 v[U];
+    // LDS row y - y0 + 1; one 4-byte word (both channels) per pixel, four
+    // loads in flight per thread before their LDS stores
+    const int q0 = max(y0 - 1, 0) * W, q1 = min(a.npx, (y0 + BAND + 1) * W);
+    const uint32_t *src2 = (const uint32_t *)(a.in + (size_t)s * a.npx * 2);
+    constexpr int U = 4;
+    for (int i0 = q0 + tid; i0 < q1; i0 += CT * U) {
+        uint32_t v[U];
 #pragma unroll
-            for (int e = 0; e < U; ++e) {
-                const int i = i0 + e * CTM;
-                v[e] = i < n8 ? src4[i] : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int e = 0; e < U; ++e) {
-                const int i = i0 + e * CTM;
-                if (i < n8) {
-                    const int p = q0 + i / C8, c8 = i % C8, y = p / W, x = p % W;
-                    *(uint4 *)&act[((y - y0 + 1) * PW + (x + 1)) * CIN + 8 * c8] = v[e];
-                }
-            }
+        for (int e = 0; e < U; ++e) {
+            const int i = i0 + e * CT;
+            v[e] = i < q1 ? src2[i] : 0u;
         }
-    } else {
-        static_assert(CIN == 2, "the input layer has two channels");
-        // one 4-byte word (both channels) per pixel, four loads in flight per
-        // thread before their LDS stores
-        constexpr int U = 4;
-        const uint32_t *src2 = (const uint32_t *)src;
-        for (int i0 = q0 + tid; i0 < q1; i0 += CTM * U) {
-            uint32_t v[U];
 #pragma unroll
-            for (int e = 0; e < U; ++e) {
-                const int i = i0 + e * CTM;
-                v[e] = i < q1 ? src2[i] : 0u;
-            }
-#pragma unroll
-            for (int e = 0; e < U; ++e) {
-                const int i = i0 + e * CTM;
-                if (i < q1) {
-                    const int y = i / W, x = i % W;
-                    *(uint32_t *)&act[((y - y0 + 1) * PW + (x + 1)) * 2] = v[e];
-                }
+        for (int e = 0; e < U; ++e) {
+            const int i = i0 + e * CT;
+            if (i < q1) {
+                const int y = i / W, x = i % W;
+                *(uint32_t *)&act[((y - y0 + 1) * PW + (x + 1)) * 2] = v[e];
             }
         }
     }
     __syncthreads();
     bf16 *dst = a.out + (size_t)s * a.npx * 32;
-    // A operand of tile t, step ks: pixel t*16 + col, inputs k = ks*32 + 8g .. +7
-    auto load_a = [&](int t, int ks) -> bf16x8 {
-        bf16x8 A;
+    const float b0 = a.bias[2 * col], b1 = a.bias[2 * col + 1];
+    const int ntile = (p1 - p0 + 15) / 16;
+    for (int t = wave; t < ntile; t += CNW) {
+        // A operand: pixel t*16 + col, inputs k = 8g .. +7: both channels of
+        // taps 4g .. +3, one 4-byte word each
         const int p = p0 + t * 16 + col, y = p / W - y0, x = p % W;
-        const bool pin = p < p1;
-        if constexpr (CIN == 32) {
-            const int dy = ks / 3 - 1, dx = ks % 3 - 1;
-            if (pin) {
-                A = *(const bf16x8 *)&act[((y + 1 + dy) * PW + (x + 1 + dx)) * 32 + 8 * g];
-            } else {
+        bf16x8 A;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) A[e] = (bf16)0.f;
+        for (int e2 = 0; e2 < 4; ++e2) {
+            const int tap = 4 * g + e2;
+            uint32_t w = 0u;
+            if (p < p1 && tap < 9) {
+                const int dy = tap / 3 - 1, dx = tap % 3 - 1;
+                w = *(const uint32_t *)&act[((y + 1 + dy) * PW + (x + 1 + dx)) * 2];
             }
-        } else {
-            // k = ks*32 + 8g + e is tap k / 2, channel k % 2: a lane's 8 values
-            // are both channels of taps ks*16 + 4g .. +3, one 4-byte word each
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const int tap = ks * 16 + 4 * g + e2;
-                uint32_t w = 0u;
-                if (pin && tap < 9) {
-                    const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-                    w = *(const uint32_t *)&act[((y + 1 + dy) * PW + (x + 1 + dx)) * 2];
-                }
-                A[2 * e2] = __builtin_bit_cast(bf16, (uint16_t)(w & 0xffffu));
-                A[2 * e2 + 1] = __builtin_bit_cast(bf16, (uint16_t)(w >> 16));
-            }
+            A[2 * e2] = __builtin_bit_cast(bf16, (uint16_t)(w & 0xffffu));
+            A[2 * e2 + 1] = __builtin_bit_cast(bf16, (uint16_t)(w >> 16));
         }
-        return A;
-    };
-    // the backward pass's gates (channels 2 col, 2 col + 1 of pixels 4g ..
-    // 4g+3 of tile t), loaded before the tile's products so they are in flight
-    auto load_gate = [&](int t, uint32_t (&gw)[4]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int pp = p0 + t * 16 + 4 * g + r;
-            gw[r] = (MODE == 1 && pp < p1)
-                        ? *(const uint32_t *)&a.gate[((size_t)s * a.npx + pp) * 32 + 2 * col]
-                        : 0u;
-        }
-    };
-    // pixels 4g .. 4g+3 of tile t, channels 2 col and 2 col + 1: one 4-byte
-    // store per pixel
-    float ps0 = 0.f, ps1 = 0.f;                 // channel sums of the stored outputs (forward)
-    auto store = [&](int t, const floatx4 &r0, const floatx4 &r1, const uint32_t (&gw)[4]) {
-        float b0 = 0.f, b1 = 0.f;
-        if (MODE == 0) {
-            b0 = a.bias[2 * col];
-            b1 = a.bias[2 * col + 1];
-        }
+        const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+        const floatx4 r0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B0, z, 0, 0, 0);
+        const floatx4 r1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B1, z, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int pp = p0 + t * 16 + 4 * g + r;
             if (pp >= p1) continue;
-            float v0 = r0[r], v1 = r1[r];
-            if (MODE == 0) {
-                v0 = fmaxf(v0 + b0, 0.f);
-                v1 = fmaxf(v1 + b1, 0.f);
-            } else {
-                const bf16 *gv = (const bf16 *)&gw[r];
-                v0 = bf2f(gv[0]) > 0.f ? v0 : 0.f;
-                v1 = bf2f(gv[1]) > 0.f ? v1 : 0.f;
-            }
-            const bf16 o2[2] = {(bf16)v0, (bf16)v1};
+            const bf16 o2[2] = {(bf16)fmaxf(r0[r] + b0, 0.f), (bf16)fmaxf(r1[r] + b1, 0.f)};
             *(uint32_t *)&dst[(size_t)pp * 32 + 2 * col] = *(const uint32_t *)o2;
-            if (MODE == 0) {
-                ps0 += bf2f(o2[0]);
-                ps1 += bf2f(o2[1]);
-            }
+        }
+    }
+}
+
+// The 32-channel layers (K = 288).  A wave owns 8 output rows of one 16-pixel
+// half of the width (column 31 of the right half is computed and dropped): it
+// walks down the input rows, and each row's three shifted reads feed the three
+// output rows that touch it, in tap order, so an activation is read three
+// times instead of nine, and no address is computed past the first (all are
+// constants off it).  The weights are the A operand, with rows permuted so
+// that a lane ends with eight consecutive channels of one pixel: one 16-byte
+// store (and gate load).  LDS rows are 32 pixels apart and share one zero
+// column between a row's right and the next row's left border, so staging is
+// linear.  A workgroup stays (two per CU, so that the weights, the window and
+// the next band fit its registers) and loads its next band while it convolves:
+// one band per workgroup, all resident at once, loaded, computed and stored in
+// step.  Per 512 stamps: 24 -> 19 us forward, 27 -> 19.5 us backward; the floor is
+// 62 and 93 MB of activations, 10 and 15 us.  Three per CU: 1024 bands over 768,
+// slower than before.
+template <int MODE>
+__global__ __launch_bounds__(CT, CPW) void cnn_conv32_kernel(ConvArgs a) {
+    constexpr int KP = 288, W = 31, HR = 8;
+    // [18][32 pixels][32]: pixel 0 of a row is x = -1; two pixels past the end
+    // are read for column 31
+    __shared__ __align__(16) uint4 act[(AROWS * 32 + 2) * 4];
+    const int nwork = *a.nvalid * NBAND;
+    int work = blockIdx.x;
+    if (work >= nwork) return;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6, col = lane & 15, g = lane >> 4;
+    // input rows: 124 pieces of 16 bytes each, then four of zeros
+    const int q = tid & 127, rq = tid >> 7;
+    uint4 v[AROWS / 2];
+    int s = a.order[work / NBAND];
+    auto fetch = [&](int wk, int st) {
+        const uint4 *src = (const uint4 *)(a.in + (size_t)st * a.npx * 32);
+        const int y0 = (wk % NBAND) * BAND;
+#pragma unroll
+        for (int k = 0; k < AROWS / 2; ++k) {
+            const int y = y0 - 1 + 2 * k + rq;
+            v[k] = q < 124 && y >= 0 && y < W ? src[y * 124 + q] : make_uint4(0u, 0u, 0u, 0u);
         }
     };
-    // two tiles per pass (t and t + NW): four independent accumulator chains
-    constexpr int NW = CTM / 64;
-    const int ntile = (p1 - p0 + 15) / 16;
-    for (int t = wave; t < ntile; t += 2 * NW) {
-        const bool two = t + NW < ntile;                // uniform across the wave
-        uint32_t g0[4], g1[4];
-        load_gate(t, g0);
-        if (two) load_gate(t + NW, g1);
-        floatx4 p0 = {0.f, 0.f, 0.f, 0.f}, p1 = p0, q0 = p0, q1 = p0;
+    fetch(work, s);
+    // weights: row i of the first operand is channel 8 (i / 4) + i % 4, of the
+    // second 4 more
+    bf16x8 A0[9], A1[9];
+    {
+        const bf16 *w = a.w + (8 * (col >> 2) + (col & 3)) * KP + 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 A = load_a(t, ks);
-            p0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B0[ks], p0, 0, 0, 0);
-            p1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B1[ks], p1, 0, 0, 0);
-            if (two) {
-                const bf16x8 A2 = load_a(t + NW, ks);
-                q0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2, B0[ks], q0, 0, 0, 0);
-                q1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2, B1[ks], q1, 0, 0, 0);
+        for (int ks = 0; ks < 9; ++ks) A0[ks] = *(const bf16x8 *)(w + ks * 32);
+#pragma unroll
+        for (int ks = 0; ks < 9; ++ks) A1[ks] = *(const bf16x8 *)(w + 4 * KP + ks * 32);
+    }
+    if (tid < 4) act[tid] = make_uint4(0u, 0u, 0u, 0u);
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < AROWS / 2; ++k) act[(2 * k + rq) * 128 + 4 + q] = v[k];
+        __syncthreads();
+        const int y0 = (work % NBAND) * BAND;
+        const int next = work + gridDim.x;
+        int sn = 0;
+        if (next < nwork) {
+            sn = a.order[next / NBAND];
+            fetch(next, sn);
+        }
+        const int x = (wave & 1) * 16 + col, R0 = (wave >> 1) * HR;
+        const int nrow = min(HR, min(BAND, W - y0) - R0);
+        const bool in = x < W;
+        const size_t o0 = ((size_t)s * a.npx + (y0 + R0) * W + x) * 32 + 8 * g;
+        const uint4 *rd = act + (R0 * 32 + x) * 4 + g;
+        float bias[8];
+        if (MODE == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bias[e] = a.bias[8 * g + e];
+        }
+        floatx4 acc[3][2];
+        uint4 gate[3];
+#pragma unroll
+        for (int it = 0; it < HR + 2; ++it) {
+            if (MODE == 1 && it < HR)
+                gate[it % 3] = in && it < nrow ? *(const uint4 *)(a.gate + o0 + (size_t)it * W * 32)
+                                               : make_uint4(0u, 0u, 0u, 0u);
+            if (it < HR) acc[it % 3][0] = acc[it % 3][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const uint4 b = rd[(it * 32 + dx) * 4];
+                const bf16x8 B = *(const bf16x8 *)&b;
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int j = it - dy;
+                    if (j >= 0 && j < HR) {
+                        acc[j % 3][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A0[dy * 3 + dx], B, acc[j % 3][0], 0, 0, 0);
+                        acc[j % 3][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1[dy * 3 + dx], B, acc[j % 3][1], 0, 0, 0);
+                    }
+                }
+            }
+            const int j = it - 2;
+            if (j >= 0) {
+                bf16x8 o;
+                const bf16 *gv = (const bf16 *)&gate[(j + 3) % 3];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float r = acc[(j + 3) % 3][e >> 2][e & 3];
+                    if (MODE == 0) r = fmaxf(r + bias[e], 0.f);
+                    else r = bf2f(gv[e]) > 0.f ? r : 0.f;
+                    o[e] = (bf16)r;
+                }
+                if (in && j < nrow) *(bf16x8 *)(a.out + o0 + (size_t)j * W * 32) = o;
             }
         }
-        store(t, p0, p1, g0);
-        if (two) store(t + NW, q0, q1, g1);
-    }
-    if (MODE == 0 && a.pool) {
-        // the spatial sum of the band (the head's pooling, fused): lanes col,
-        // col + 16, col + 32, col + 48 hold the same two channels, then the
-        // waves are added in order through LDS
-        ps0 += __shfl_xor(ps0, 16);
-        ps0 += __shfl_xor(ps0, 32);
-        ps1 += __shfl_xor(ps1, 16);
-        ps1 += __shfl_xor(ps1, 32);
-        float *red = (float *)sm;               // [NW][32], after every wave is done with act
-        __syncthreads();
-        if (g == 0) {
-            red[wave * 32 + 2 * col] = ps0;
-            red[wave * 32 + 2 * col + 1] = ps1;
-        }
-        __syncthreads();
-        if (tid < 32) {
-            float sum = 0.f;
+        if (MODE == 0 && a.pool) {
+            // the spatial sum of the band (the head's pooling, fused), of the
+            // stored outputs: lane (col, g) takes channels 2 col, 2 col + 1 of
+            // pixels 4g .. 4g+3 of its wave's raster tiles, the four g are added,
+            // then the waves in order through LDS
+            __threadfence_block();
+            __syncthreads();
+            const bf16 *dst = a.out + (size_t)s * a.npx * 32;
+            const int p0 = y0 * W, p1 = min(a.npx, p0 + BAND * W), ntile = (p1 - p0 + 15) / 16;
+            float ps0 = 0.f, ps1 = 0.f;
+            uint32_t w[8][4];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) sum += red[w * 32 + tid];
-            a.pool[((size_t)s * CS::NBAND + blockIdx.x % CS::NBAND) * 32 + tid] = sum;
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int pp = min(p0 + (wave + CNW * k) * 16 + 4 * g + r, p1 - 1);
+                    w[k][r] = *(const uint32_t *)&dst[(size_t)pp * 32 + 2 * col];
+                }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (p0 + (wave + CNW * k) * 16 + 4 * g + r < p1) {
+                        const bf16 *o2 = (const bf16 *)&w[k][r];
+                        ps0 += bf2f(o2[0]);
+                        ps1 += bf2f(o2[1]);
+                    }
+                }
+            static_assert(8 * CNW * 16 >= BAND * W, "eight tiles per wave cover a band");
+            ps0 += __shfl_xor(ps0, 16);
+            ps0 += __shfl_xor(ps0, 32);
+            ps1 += __shfl_xor(ps1, 16);
+            ps1 += __shfl_xor(ps1, 32);
+            float *red = (float *)act;              // [CNW][32]
+            if (g == 0) {
+                red[wave * 32 + 2 * col] = ps0;
+                red[wave * 32 + 2 * col + 1] = ps1;
+            }
+            __syncthreads();
+            if (tid < 32) {
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < CNW; ++k) sum += red[k * 32 + tid];
+                a.pool[((size_t)s * NBAND + work % NBAND) * 32 + tid] = sum;
+            }
         }
+        if (next >= nwork) break;
+        __syncthreads();
+        if (MODE == 0 && tid < 4) act[tid] = make_uint4(0u, 0u, 0u, 0u);   // (the pooling's sums lay there)
+        work = next;
+        s = sn;
     }
 }
 
@@ -1384,12 +1417,12 @@ __global__ __launch_bounds__(NTS) void stamps_kernel(StampArgs a, uint32_t cap) 
 
 template <int CIN, int MODE>
 int conv_launch(argus_ctx *ctx, const ConvArgs &ca) {
-    size_t lds = (size_t)ConvShape<CIN>::ACT * sizeof(bf16);
-    ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute((const void *)cnn_conv_kernel<CIN, MODE>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((cnn_conv_kernel<CIN, MODE>), dim3(ca.n * ConvShape<CIN>::NBAND),
-                       dim3(conv_threads<MODE>()), lds,
-                       ctx->stream, ca);
+    static_assert(CIN == 32 || (CIN == 2 && MODE == 0), "first layer forward, the others both ways");
+    const dim3 grid(ca.n * NBAND);
+    if constexpr (CIN == 32)
+        hipLaunchKernelGGL(cnn_conv32_kernel<MODE>, dim3(std::min(ca.n * NBAND, ctx->n_cu * CPW)), dim3(CT), 0, ctx->stream, ca);
+    else
+        hipLaunchKernelGGL(cnn_conv2_kernel, grid, dim3(CT), 0, ctx->stream, ca);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
