@@ -4,11 +4,16 @@
 // Per output pixel p the kernel is evaluated at p (K_p = sum_m P_m(p) K_m).
 // Along a row yt is fixed, so with the stamps ordered (p,q) = (0,0),(0,1),
 // (0,2),(1,0),(1,1),(2,0):  K_p = A0 + xt (A1 + xt A2), A0 = K0 + yt (K1 +
-// yt K2), A1 = K3 + yt K4, A2 = K5.  A thread owns 8 consecutive pixels of a
-// row: the A's of a tap are evaluated once for its row and shared by the 8
-// pixels, the reference and variance windows of a kernel row sit in
-// registers, and each tap costs 5 VALU ops per pixel (2 for a constant
-// kernel).  Workgroups are 128x16 output pixels with an h-pixel halo in LDS.
+// yt K2), A1 = K3 + yt K4, A2 = K5.  A thread owns 8 (or, on smaller frames, 4)
+// consecutive pixels of a row: the A's of a tap are evaluated once for its row
+// and shared by the pixels, the reference and variance windows of a kernel row
+// sit in registers, and each tap costs 5 VALU ops per pixel (2 for a constant
+// kernel).  Workgroups are 128x16 (64x16) output pixels with an h-pixel halo in
+// LDS.  VALU-bound: 3.8 ms of the full frame at 21x21, degree 2, where the FMAs
+// alone take 3.4.  With four pixels the taps' polynomials come by scalar loads:
+// as LDS reads, two per tap whatever the pixels, they would take as long as the
+// FMAs (1500x1000, degree 1: 372 -> 361 us for the whole difference); with
+// eight, scalar loads are slower (full frame 9.16 -> 9.91 ms).
 #include <mutex>
 
 #include "internal.h"
@@ -21,7 +26,7 @@ static __device__ __align__(256) double scratch[(size_t)ARGUS_NOALLOC_MAX_BLOCKS
 
 namespace {
 
-constexpr int BW = 128, BH = 16, PXT = 8, NTHR = 256;
+constexpr int BH = 16, NTHR = 256;
 
 struct SubArgs {
     const float *stamps, *bg;
@@ -38,26 +43,30 @@ struct SubArgs {
     int write;                 // 0: only the sums (diff, dvar, dmask are null)
 };
 
-template <int HH>
+template <int HH, int PXT>
 struct SubLds {
+    static constexpr int BW = 16 * PXT;                 // 16 threads of a row, PXT pixels each
     static constexpr int K = 2 * HH + 1;
     static constexpr int TH = BH + 2 * HH;
     static constexpr int TWr = BW + 2 * HH;
     static constexpr int TW = (TWr + 3) & ~3;          // float row stride, 16-byte aligned
     static constexpr int MW = (TWr + 15) & ~15;         // mask row stride
+    // the taps' values come by scalar loads instead of LDS
+    __host__ __device__ static constexpr bool scalar_taps(int D) { return D > 0 && PXT == 4; }
 };
 
-template <int D, int HH>
+template <int D, int HH, int PXT>
 __global__ __launch_bounds__(NTHR) void subtract_kernel(SubArgs a) {
-    using L = SubLds<HH>;
-    constexpr int K = L::K, TH = L::TH, TW = L::TW, MW = L::MW, NP = (D + 1) * (D + 2) / 2;
+    using L = SubLds<HH, PXT>;
+    constexpr int BW = L::BW, K = L::K, TH = L::TH, TW = L::TW, MW = L::MW, NP = (D + 1) * (D + 2) / 2;
     constexpr int NS = (D == 0) ? 2 : NP;               // constant kernel also keeps K^2
     constexpr int NSP = NS <= 4 ? 4 : 8;                // per-tap values, padded to 16-byte reads
+    constexpr bool SCALAR = L::scalar_taps(D);
     extern __shared__ float lds[];
     float *Rt = lds;                                    // [TH][TW]
     float *Vt = Rt + TH * TW;                           // [TH][TW]
     float *St = Vt + TH * TW;                           // [K*K][NSP] stamp values per tap
-    uint8_t *Mt = (uint8_t *)(St + NSP * K * K);        // [TH][MW] ref mask != 0
+    uint8_t *Mt = (uint8_t *)(St + (SCALAR ? 0 : NSP * K * K));   // [TH][MW] ref mask != 0
     uint8_t *Mr = Mt + TH * MW;                         // [TH][BW] row-OR over 2h+1
     __shared__ double red[4][NTHR / 64];
 
@@ -112,7 +121,7 @@ __global__ __launch_bounds__(NTHR) void subtract_kernel(SubArgs a) {
             }
         }
         const float *src = a.stamps + (size_t)reg * NP * K * K;
-        {
+        if constexpr (!SCALAR) {
             constexpr int NS_ = (NP * K * K + NTHR - 1) / NTHR;
             float sv_[NS_];
 #pragma unroll
@@ -174,15 +183,19 @@ __global__ __launch_bounds__(NTHR) void subtract_kernel(SubArgs a) {
                 }
 #pragma unroll
                 for (int uu = 0; uu < K; ++uu) {
-                    // this tap's stamp values, one or two 16-byte reads
+                    // this tap's stamp values
                     float st[NSP];
-                    {
+                    if constexpr (!SCALAR) {
                         const float4 *sp = (const float4 *)(St + (vv * K + uu) * NSP);
 #pragma unroll
                         for (int e = 0; e < NSP / 4; ++e) {
                             const float4 v4 = sp[e];
                             st[4 * e] = v4.x; st[4 * e + 1] = v4.y; st[4 * e + 2] = v4.z; st[4 * e + 3] = v4.w;
                         }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < NP; ++e)
+                            st[e] = *(const __attribute__((address_space(4))) float *)(src + e * K * K + vv * K + uu);
                     }
                     if constexpr (D == 0) {
                         const float k = st[0], k2 = st[1];
@@ -275,15 +288,19 @@ __global__ __launch_bounds__(NTHR) void subtract_kernel(SubArgs a) {
             const int64_t o0 = orow + X0;
             if (!a.write) {
                 // chi^2 pass of the fit: no images written
-            } else if (a.vec && (X0 & 7) == 0 && X0 + PXT <= bx1) {
-                *(float4 *)(a.diff + o0) = make_float4(outd[0], outd[1], outd[2], outd[3]);
-                *(float4 *)(a.diff + o0 + 4) = make_float4(outd[4], outd[5], outd[6], outd[7]);
-                *(float4 *)(a.dvar + o0) = make_float4(outv[0], outv[1], outv[2], outv[3]);
-                *(float4 *)(a.dvar + o0 + 4) = make_float4(outv[4], outv[5], outv[6], outv[7]);
-                uint2 mo;
-                mo.x = outm[0] | (outm[1] << 8) | (outm[2] << 16) | ((uint32_t)outm[3] << 24);
-                mo.y = outm[4] | (outm[5] << 8) | (outm[6] << 16) | ((uint32_t)outm[7] << 24);
-                *(uint2 *)(a.dmask + o0) = mo;
+            } else if (a.vec && X0 % PXT == 0 && X0 + PXT <= bx1) {
+#pragma unroll
+                for (int i = 0; i < PXT; i += 4) {
+                    *(float4 *)(a.diff + o0 + i) = make_float4(outd[i], outd[i + 1], outd[i + 2], outd[i + 3]);
+                    *(float4 *)(a.dvar + o0 + i) = make_float4(outv[i], outv[i + 1], outv[i + 2], outv[i + 3]);
+                }
+                uint32_t mo[PXT / 4];
+#pragma unroll
+                for (int i = 0; i < PXT; i += 4)
+                    mo[i / 4] = outm[i] | (outm[i + 1] << 8) | (outm[i + 2] << 16) |
+                                ((uint32_t)outm[i + 3] << 24);
+                if constexpr (PXT == 8) *(uint2 *)(a.dmask + o0) = make_uint2(mo[0], mo[1]);
+                else *(uint32_t *)(a.dmask + o0) = mo[0];
             } else {
 #pragma unroll
                 for (int i = 0; i < PXT; ++i) {
@@ -349,25 +366,27 @@ __global__ __launch_bounds__(RED_THREADS) void chi2_reduce_kernel(
     }
 }
 
-template <int D, int HH>
+template <int D, int HH, int PXT>
 int sub_launch(argus_ctx *ctx, SubArgs &a, int n_blocks) {
-    using L = SubLds<HH>;
+    using L = SubLds<HH, PXT>;
     constexpr int NP = (D + 1) * (D + 2) / 2;
     constexpr int NS = (D == 0) ? 2 : NP;
     constexpr int NSP = NS <= 4 ? 4 : 8;
-    size_t lds = (size_t)2 * L::TH * L::TW * 4 + (size_t)NSP * L::K * L::K * 4 +
-                 (size_t)L::TH * L::MW + (size_t)L::TH * BW;
-    ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute((const void *)subtract_kernel<D, HH>,
+    size_t lds = (size_t)2 * L::TH * L::TW * 4 + (size_t)(L::scalar_taps(D) ? 0 : NSP) * L::K * L::K * 4 +
+                 (size_t)L::TH * L::MW + (size_t)L::TH * L::BW;
+    ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute((const void *)subtract_kernel<D, HH, PXT>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((subtract_kernel<D, HH>), dim3(n_blocks), dim3(NTHR), lds, ctx->stream, a);
+    hipLaunchKernelGGL((subtract_kernel<D, HH, PXT>), dim3(n_blocks), dim3(NTHR), lds, ctx->stream, a);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
 
 template <int D>
-int sub_dispatch_h(argus_ctx *ctx, SubArgs &a, int h, int n_blocks) {
+int sub_dispatch_h(argus_ctx *ctx, SubArgs &a, int h, int pxt, int n_blocks) {
     switch (h) {
-#define ARGUS_SH(HH) case HH: return sub_launch<D, HH>(ctx, a, n_blocks);
+#define ARGUS_SH(HH)                                                                                 \
+    case HH:                                                                                         \
+        return pxt == 8 ? sub_launch<D, HH, 8>(ctx, a, n_blocks) : sub_launch<D, HH, 4>(ctx, a, n_blocks);
         ARGUS_SH(1) ARGUS_SH(2) ARGUS_SH(3) ARGUS_SH(4) ARGUS_SH(5) ARGUS_SH(6) ARGUS_SH(7)
         ARGUS_SH(8) ARGUS_SH(9) ARGUS_SH(10) ARGUS_SH(11) ARGUS_SH(12) ARGUS_SH(13)
         ARGUS_SH(14) ARGUS_SH(15)
@@ -413,8 +432,19 @@ int launch_subtract(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec,
     const bool global = spec->mode == ARGUS_FIT_GLOBAL;
     a.RX = global ? 1 : spec->tiles_x;
     a.RY = global ? 1 : spec->tiles_y;
-    a.bpx = ((d.width + a.RX - 1) / a.RX + BW - 1) / BW;
+    const int rw = (d.width + a.RX - 1) / a.RX;
     a.bpy = ((d.height + a.RY - 1) / a.RY + BH - 1) / BH;
+    auto columns = [&](int p) { return (rw + 16 * p - 1) / (16 * p); };
+    // Pixels of a row per thread.  Four give twice the blocks: on small frames
+    // each is done in half the time, on all but the largest the last round of
+    // blocks is shorter; eight share a tap's loads and polynomial among more
+    // pixels.  Whole difference, eight / four, degree 1 and 2 (us): 256x224 134 /
+    // 122, 1100x977 370 / 348, 4500x3000 2981 / 2876, 6000x4000 (11750 blocks)
+    // 4709 / 4645, 9568x6380 (29925) 9157 / 9244.  Degree 0, which has half the
+    // work to share: 600x500 (160 blocks) 111 / 108, 2000x1500 379 / 384.
+    const int64_t blocks8 = (int64_t)a.RX * a.RY * columns(8) * a.bpy;
+    const int pxt = blocks8 < (a.D > 0 ? 16384 : 256) ? 4 : 8;
+    a.bpx = columns(pxt);
     a.sx = d.width > 1 ? 2.0 / (d.width - 1) : 0.0;
     a.sy = d.height > 1 ? 2.0 / (d.height - 1) : 0.0;
     a.vec = (d.pitch % 8 == 0) && aligned(diff, 32) && aligned(diff_var, 32) && aligned(diff_mask, 8);
@@ -438,9 +468,9 @@ int launch_subtract(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec,
     }
     if (!noalloc) argus_time_begin(ctx);
     switch (a.D) {
-        case 0: rc = sub_dispatch_h<0>(ctx, a, spec->half_width, n_blocks); break;
-        case 1: rc = sub_dispatch_h<1>(ctx, a, spec->half_width, n_blocks); break;
-        default: rc = sub_dispatch_h<2>(ctx, a, spec->half_width, n_blocks); break;
+        case 0: rc = sub_dispatch_h<0>(ctx, a, spec->half_width, pxt, n_blocks); break;
+        case 1: rc = sub_dispatch_h<1>(ctx, a, spec->half_width, pxt, n_blocks); break;
+        default: rc = sub_dispatch_h<2>(ctx, a, spec->half_width, pxt, n_blocks); break;
     }
     if (rc) return rc;
     if (!noalloc) argus_time_end(ctx, "subtract");
