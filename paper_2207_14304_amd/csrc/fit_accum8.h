@@ -62,6 +62,8 @@ struct FitLds8 {
         size_t w = 2 * INP + 2 * 32 * CKM + 2 * (S::NA + S::NRA) * SW + (TS ? 2 * TSB : 0);
         size_t b = w * 4 + (size_t)2 * (S::NA + S::NRA) * SW * 8 + 4 * 8;
         size_t rhs = (size_t)2 * nwm * S::NR * 32 * 8;   // end-of-kernel reuse
+        // (four MFMA waves, FP64: for degrees 0 and 1 also their sums, 768 each)
+        if (nwm == 4 && D <= 1 && rhs < 4 * 768 * 8) rhs = 4 * 768 * 8;
         return (b > rhs ? b : rhs) + 64;
     }
     __device__ FitLds8(float *lds) {
@@ -85,6 +87,12 @@ struct FitLds8 {
 template <bool TS>
 __device__ __forceinline__ int fit8_strip_steps(int rows) { return fit8_steps(rows + (TS ? 2 : 1)); }
 
+// Taps 0..15 of a filter (of which h + 1 are used) in scalar registers.
+typedef float Taps16 __attribute__((ext_vector_type(16), aligned(4)));
+__device__ __forceinline__ Taps16 load_taps(const float *p) {
+    return *(const __attribute__((address_space(4))) Taps16 *)p;
+}
+
 // Convolution wave cw (wave-uniform) of the NWC convolution waves, with up
 // to NP planes (from plist8 for 8 waves, plist for 4).  Wave 0 (W0) also
 // stages the fit-set weights (with 8 waves it takes one plane, so that its
@@ -99,6 +107,8 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
     using L = FitLds8<D, HH, TS>;
     constexpr int K = L::K;
     constexpr int NR_ = K - 1 + U8;                      // window registers per plane
+    constexpr bool KEEP = NP <= 2;                       // four planes' row filters do not fit the
+                                                         // scalar registers: loaded per step
     const int tid = threadIdx.x, lane = tid & 63;
     L l(lds);
     int count = 0;
@@ -213,6 +223,11 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
             const bool outrow = live && yy >= ry0 + HH;
             if (W0 && outrow) fetch_w(yy + 1 - HH);
             {
+                // (the tables' address is hidden from the loop, so that the
+                // coefficients are read where they are used instead of being
+                // kept, and spilled, across it)
+                const BasisTables *tab = a.tab;
+                asm volatile("" : "+s"(tab));
                 // row pass: taps +-v of the input row paired
                 {
                     const float *ir = l.inrow + buf * L::INP + lane + HH;
@@ -226,15 +241,18 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
                     }
 #pragma unroll
                     for (int j = 0; j < NP; ++j) {
+                        Taps16 rt;
+                        if constexpr (!KEEP) rt = load_taps(&tab->rowf[pl[j] >= 0 ? pl[j] : 0][HH]);
+                        auto tap = [&](int v) { return KEEP ? rc[j][v] : rt[v]; };
                         float acc;
                         if (odd[j]) {
-                            acc = rc[j][1] * sm[1];
+                            acc = tap(1) * sm[1];
 #pragma unroll
-                            for (int v = 2; v <= HH; ++v) acc += rc[j][v] * sm[v];
+                            for (int v = 2; v <= HH; ++v) acc += tap(v) * sm[v];
                         } else {
-                            acc = rc[j][0] * c;
+                            acc = tap(0) * c;
 #pragma unroll
-                            for (int v = 1; v <= HH; ++v) acc += rc[j][v] * sp[v];
+                            for (int v = 1; v <= HH; ++v) acc += tap(v) * sp[v];
                         }
                         rw[j][K - 1 + u] = acc;
                     }
@@ -251,7 +269,9 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
                     float *cv = l.cvec(buf);
 #pragma unroll
                     for (int j = 0; j < NP; ++j) {
-                        if (nk[j] > 0) {
+                        int n = nk[j];                   // (hidden too: its comparisons likewise)
+                        asm volatile("" : "+s"(n));
+                        if (n > 0) {
                             // even column powers on the paired sums, then odd
                             // ones on the paired differences
                             float e[HH + 1];
@@ -260,24 +280,24 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
                             for (int v = 1; v <= HH; ++v) e[v] = rw[j][u + HH - v] + rw[j][u + HH + v];
 #pragma unroll
                             for (int q = 0; q < 7; q += 2) {
-                                if (q < nk[j]) {
-                                    const float *f = &a.tab->colf[k0[j] + q][HH];
-                                    float acc = uload(f) * e[0];
+                                if (q < n) {
+                                    const Taps16 f = load_taps(&tab->colf[k0[j] + q][HH]);
+                                    float acc = f[0] * e[0];
 #pragma unroll
-                                    for (int v = 1; v <= HH; ++v) acc += uload(f + v) * e[v];
+                                    for (int v = 1; v <= HH; ++v) acc += f[v] * e[v];
                                     cv[(k0[j] + q) * L::CKM + lane] = acc;
                                 }
                             }
-                            if (nk[j] > 1) {
+                            if (n > 1) {
 #pragma unroll
                                 for (int v = 1; v <= HH; ++v) e[v] = rw[j][u + HH - v] - rw[j][u + HH + v];
 #pragma unroll
                                 for (int q = 1; q < 7; q += 2) {
-                                    if (q < nk[j]) {
-                                        const float *f = &a.tab->colf[k0[j] + q][HH];
-                                        float acc = uload(f + 1) * e[1];
+                                    if (q < n) {
+                                        const Taps16 f = load_taps(&tab->colf[k0[j] + q][HH]);
+                                        float acc = f[1] * e[1];
 #pragma unroll
-                                        for (int v = 2; v <= HH; ++v) acc += uload(f + v) * e[v];
+                                        for (int v = 2; v <= HH; ++v) acc += f[v] * e[v];
                                         cv[(k0[j] + q) * L::CKM + lane] = acc;
                                     }
                                 }
@@ -591,6 +611,146 @@ __device__ void fit_mfma8(const FitArgs &a, float *lds, int sx_begin, int sx_end
     for (int i = 0; i < S::NR; ++i) rhsbuf[((MW * 2 + half) * S::NR + i) * 32 + k] = RF[i];
 }
 
+// MFMA wave m of the four of the FP64 form for degrees 0 and 1: the moments of
+// its 16 of the row's 64 pixels for every (power, block pair) and the
+// right-hand side, so that an operand is read from LDS, widened and fixed up
+// once for all its products, and the four waves carry the same load.  The
+// xt-moments of the rows accumulate in the MFMA accumulators without a flush;
+// their yt-moments come from running sums of those accumulators: with F0 =
+// sum_i g_i after each row, F1 += F0 and F2 += F1 leave F1 = sum r g, F2 = sum
+// r (r + 1) / 2 g with r = n - i the rows left, and yt = yt_n - r sy.  Degree 2
+// keeps the split by tasks: its 45 sums of 8 registers do not fit a wave.
+// 2394x1597, degree 1, 21x21: 781 -> 664 us with the spills of the filters'
+// coefficients below (MFMA busy 40% of the SIMD cycles, VALU 31%, at one
+// convolution and one MFMA wave per SIMD; reading a filter ahead spills: 720).
+template <int D, int HH>
+__device__ void fit_mfma64(const FitArgs &a, float *lds, int ry0, int ry1, bool active, int m,
+                           double *part) {
+    using S = FitShape<D>;
+    using L = FitLds8<D, HH, false>;
+    constexpr int NB = 2 * D + 1;
+    const int lane = threadIdx.x & 63, col = lane & 15, pk = lane >> 4;
+    L l(lds);
+    doublex4 F[S::NA][3][NB];                            // b <= 2D - a
+    double T[S::NRA][2][D + 1];                          // b <= D - e
+#pragma unroll
+    for (int e = 0; e < S::NA; ++e)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) F[e][j][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < S::NRA; ++e)
+#pragma unroll
+        for (int b = 0; b <= D; ++b) T[e][0][b] = T[e][1][b] = 0.0;
+    const double g0 = col < a.nb ? (double)a.tab->gam[col] : 0.0;
+    const double g1 = 16 + col < a.nb ? (double)a.tab->gam[16 + col] : 0.0;
+    const int ystart = ry0 - HH, yend = active ? ry1 + HH : ystart, p = 16 * m + 4 * pk;
+    const int ys0 = ystart & ~1;
+    const int ylast = ys0 + fit8_strip_steps<false>(yend - ys0) - 1;
+    __syncthreads();
+    for (int yy = ys0; yy <= ylast; ++yy) {
+        if (yy - 1 >= ry0 + HH && yy - 1 < yend) {       // output row yy - 1 - h
+            const int pb = (yy & 1) ^ 1;
+            const float *c = l.cvec(pb);
+            const float4 va = *(const float4 *)(c + col * L::CKM + p);
+            const float4 vb = *(const float4 *)(c + (16 + col) * L::CKM + p);
+            const float4 vz = *(const float4 *)(c + p);
+            const float ca[4] = {va.x, va.y, va.z, va.w}, cb[4] = {vb.x, vb.y, vb.z, vb.w};
+            const float cz[4] = {vz.x, vz.y, vz.z, vz.w};
+#pragma unroll
+            for (int i2 = 0; i2 < 4; i2 += 2) {
+                double w[S::NA][2], sw[S::NRA][2];
+#pragma unroll
+                for (int e = 0; e < S::NA; ++e) {
+                    const double2 v = *(const double2 *)(l.wxd(pb) + e * SW + p + i2);
+                    w[e][0] = v.x; w[e][1] = v.y;
+                }
+#pragma unroll
+                for (int e = 0; e < S::NRA; ++e) {
+                    const double2 v = *(const double2 *)(l.wsxd(pb) + e * SW + p + i2);
+                    sw[e][0] = v.x; sw[e][1] = v.y;
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const double z = (double)cz[i2 + i];
+                    const double c0 = (double)ca[i2 + i] + g0 * z, c1 = (double)cb[i2 + i] + g1 * z;
+#pragma unroll
+                    for (int e = 0; e < S::NA; ++e) {
+                        const double b0 = w[e][i] * c0, b1 = w[e][i] * c1;
+                        F[e][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c0, b0, F[e][0][0], 0, 0, 0);
+                        F[e][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c0, b1, F[e][1][0], 0, 0, 0);
+                        F[e][2][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c1, b1, F[e][2][0], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int e = 0; e < S::NRA; ++e) {
+                        T[e][0][0] += sw[e][i] * c0;
+                        T[e][1][0] += sw[e][i] * c1;
+                    }
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < S::NRA; ++e)
+#pragma unroll
+                for (int b = 1; b <= D - e; ++b) {
+                    T[e][0][b] += T[e][0][b - 1];
+                    T[e][1][b] += T[e][1][b - 1];
+                }
+#pragma unroll
+            for (int e = 0; e < S::NA; ++e)
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int b = 1; b <= 2 * D - e; ++b) F[e][j][b] += F[e][j][b - 1];
+        }
+        __syncthreads();
+    }
+    // yt-moments, the waves' sums through LDS (the convolution waves keep the
+    // barrier count)
+    const double yn = (double)(active ? ry1 : ry0) * a.sy - (a.sy != 0.0 ? 1.0 : 0.0), s = a.sy;
+    double *red = (double *)lds;                         // [4][768]
+#pragma unroll
+    for (int e = 0; e < S::NA; ++e)
+#pragma unroll
+        for (int b = 0; b <= 2 * D - e; ++b) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    double v = F[e][j][0][r];
+                    if (b == 1) v = yn * v - s * F[e][j][1 % NB][r];
+                    if (b == 2)
+                        v = yn * yn * v - 2.0 * yn * s * F[e][j][1 % NB][r] +
+                            s * s * (2.0 * F[e][j][2 % NB][r] - F[e][j][1 % NB][r]);
+                    red[m * 768 + j * 256 + (4 * r + pk) * 16 + col] = v;
+                }
+            __syncthreads();
+            double *g = part + (size_t)qidx(e, b, 2 * D) * 768;
+            for (int i = m * 64 + lane; i < 768; i += 256)
+                g[i] = (red[i] + red[768 + i]) + (red[1536 + i] + red[2304 + i]);
+            __syncthreads();
+        }
+    double *rhsbuf = (double *)lds;
+#pragma unroll
+    for (int e = 0; e < S::NRA; ++e)
+#pragma unroll
+        for (int b = 0; b <= D - e; ++b) {
+            double v[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v[h] = b == 0 ? T[e][h][0] : yn * T[e][h][0] - s * T[e][h][D];
+                v[h] += __shfl_xor(v[h], 16);
+                v[h] += __shfl_xor(v[h], 32);
+            }
+            rhsbuf[((m * 2 + (lane >> 5)) * S::NR + qidx(e, b, D)) * 32 + (lane & 31)] =
+                lane >= 32 ? 0.0 : lane >= 16 ? v[1] : v[0];
+        }
+}
+
+// whether fit_mfma64 takes the moments
+template <int D, int PREC>
+constexpr bool fit_by_pixels() { return PREC == ARGUS_FP64 && D <= 1; }
+
 template <int D, int HH, int PREC, int NWC, int NWM, int W>
 __device__ __forceinline__ void fit_dispatch8(int w, const FitArgs &a, float *lds, int sx0, int sx1,
                                               int ry0, int ry1, bool active, double *part) {
@@ -648,10 +808,15 @@ __global__ __launch_bounds__(64 * (NWC + NWM)) void fit_accum8_kernel(FitArgs a)
         }
     }
     int count = 0;
-    if (w == 0)
-        count = fit_conv8<D, HH, PREC, NWC, NP0, true>(a, lds, sx0, sx1, ry0, ry1, active, 0);
-    else if (w < NWC)
-        fit_conv8<D, HH, PREC, NWC, NP, false>(a, lds, sx0, sx1, ry0, ry1, active, w);
+    if (w < NWC) {
+        if (w == 0)
+            count = fit_conv8<D, HH, PREC, NWC, NP0, true>(a, lds, sx0, sx1, ry0, ry1, active, 0);
+        else
+            fit_conv8<D, HH, PREC, NWC, NP, false>(a, lds, sx0, sx1, ry0, ry1, active, w);
+        if constexpr (fit_by_pixels<D, PREC>())
+            for (int q = 0; q < 2 * S::NQ; ++q) __syncthreads();
+    } else if constexpr (fit_by_pixels<D, PREC>())
+        fit_mfma64<D, HH>(a, lds, ry0, ry1, active, w - NWC, part);
     else
         fit_dispatch8<D, HH, PREC, NWC, NWM, NWC>(w, a, lds, sx0, sx1, ry0, ry1, active, part);
     if (w == 0) {
