@@ -82,8 +82,9 @@ def log(*a):
 
 
 # Sources that decide the frame fit's memory traffic (kernel and its launch).
-FIT_SOURCES = ["paper_2207_14304_amd/csrc/fit_accum8.h", "paper_2207_14304_amd/csrc/fit_accum.h",
-               "paper_2207_14304_amd/csrc/k_fit_fp32.hip", "paper_2207_14304_amd/csrc/k_fit.hip"]
+FIT_SOURCES = ["paper_2207_14304_amd/csrc/fit_wide.h", "paper_2207_14304_amd/csrc/fit_accum8.h",
+               "paper_2207_14304_amd/csrc/fit_accum.h", "paper_2207_14304_amd/csrc/k_fit_wide.hip",
+               "paper_2207_14304_amd/csrc/k_fit.hip"]
 TRAFFIC_FILE = "profiles/frame_path_hbm_traffic.md"
 
 
@@ -255,7 +256,7 @@ def _limit_blas_threads_probe(_):
 
 
 def batch_leg(args, torch, argus, synth):
-    """Cutout batching: many cameras' frames, one persistent graph launch."""
+    """Cutout batching: many cameras' frames, one graph launch."""
     from paper_2207_14304_amd import synth_torch
     W, H, nf = args.width, args.height, args.batch_frames
     t0 = time.perf_counter()

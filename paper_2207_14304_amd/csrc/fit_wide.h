@@ -30,7 +30,7 @@
 // barrier per step.  Of the two MFMA waves of a SIMD one multiplies first and
 // the other splits first, so that matrix and vector work meet.
 //
-// Full frame, D = 2, h = 10: 7.46 -> 4.91 ms against the FP32 form, the
+// Full frame, D = 2, h = 10: 7.46 -> 4.95 ms against the FP32 form, the
 // difference image as far from the 64-bit one as before (9.0e-6 and 9.2e-6
 // relative).  Narrower frames keep the FP32 form: their |d| would need more
 // products, and the frame's 2 D + 1 powers cost them less than the solve.
