@@ -66,7 +66,10 @@ extern "C" {
 /* ---- fit modes and precisions ------------------------------------------ */
 #define ARGUS_FIT_GLOBAL   0  /* one solve; tiles only order the partial sums */
 #define ARGUS_FIT_PER_TILE 1  /* one independent solve per tile              */
-#define ARGUS_FP32   0        /* row moments on FP32 MFMA, FP64 row sums     */
+#define ARGUS_FP32   0        /* row moments to FP32 accuracy (FP32 MFMA, or on
+                               * frames of 6144 columns and more, degree 1 and 2,
+                               * six BF16 products of three-way splits), FP64
+                               * sums over rows                              */
 #define ARGUS_BF16X3 1        /* hi/lo-split BF16 MFMA, FP32 accumulation    */
 #define ARGUS_FP64   2        /* row moments on FP64 MFMA                    */
 
@@ -211,7 +214,8 @@ int argus_kernel_dims(const argus_kernel_spec *spec, int *n_unknowns, int *n_sol
  * ref_mask == 0 over the (2h+1)^2 footprint and sci_var + ref_var > 0;
  * weights w = 1/(sci_var + ref_var).  Design row of pixel p: P_m(p) *
  * (ref (x) B_k)(p) at index k*nP + m, then the background block P_m(p).
- * Normal equations are accumulated per tile (FP32 products, FP64 sums),
+ * Normal equations are accumulated per tile (products of the spec's
+ * precision summed over 64-pixel row segments, FP64 sums over those),
  * added in FP64 (all tiles for GLOBAL), Jacobi-scaled and Cholesky-solved in
  * FP64 on the GPU.  Outputs (device): coeffs f64 [n_solves][n] (NaN where the
  * solve failed), chi2 f64 [n_solves] (nullable), n_fit i64 [n_solves]

@@ -266,7 +266,13 @@ __device__ __forceinline__ float uload(const float *p) { return *(cfloat_p)p; }
 
 // One launcher per precision, each in its own translation unit.
 int fit_accum_launch_fp32(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
-// the FP32 fit of degree 1 or 2 on frames at least FIT_WIDE_MIN columns wide
+// The FP32 fit of degree 1 or 2 on frames at least FIT_WIDE_MIN columns wide
+// (fit_wide.h).  The line is not where the speed turns: the wide form is the
+// faster one on both sides of it (degree 2, 15 x 15, FP32 form / wide form:
+// 1100x977 154 / 132 us, 3000x2000 751 / 639, 6143x4100 2.85 / 2.42 ms, 9576x6388
+// 7.04 / 5.94; degree 1: 134 / 110 us, 607 / 484, 2.27 / 1.69 ms, 5.58 / 4.13).  It
+// stands where the frames' own FP32 rounding (1e-5 and more of a pixel below it)
+// would let every narrower difference move.
 int fit_accum_launch_wide(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
 constexpr int FIT_WIDE_MIN = 6144;
 int fit_accum_launch_fp64(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);

@@ -98,7 +98,8 @@ __device__ __forceinline__ Taps16 load_taps(const float *p) {
 // stages the fit-set weights (with 8 waves it takes one plane, so that its
 // registers fit the same budget); it returns the number of fit pixels it
 // counted, the others return 0.  WIDE (fit_wide.h): the weights go out as
-// sqrt(w) and sqrt(w) s xt^e, and the pipeline drains one step more.
+// sqrt(w) and sqrt(w) s d^e, d the offset from the strip's centre, and the
+// pipeline drains one step more.
 template <int D, int HH, int PREC, int NWC, int NP, bool W0, bool WIDE = false>
 __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end, int ry0,
                          int ry1, bool active, int cw) {
@@ -318,10 +319,11 @@ __device__ int fit_conv8(const FitArgs &a, float *lds, int sx_begin, int sx_end,
                             const float q = __builtin_amdgcn_sqrtf(w);
                             l.wx(buf)[lane] = q;
                             float t = q * w_s;
+                            const float d = (float)(((double)lane - 31.5) * a.sx);
 #pragma unroll
                             for (int e = 0; e < S::NRA; ++e) {
-                                l.wsx(buf)[e * SW + lane] = t * xp;
-                                xp *= xt;
+                                l.wsx(buf)[e * SW + lane] = t;
+                                t *= d;
                             }
                         } else
 #pragma unroll

@@ -7,22 +7,18 @@
 //
 // 1. Powers about the strip's centre.  With xt = x0 + d the moments are taken
 //    in powers of d, |d| <= 31.5 * 2/(W-1), which the end of the kernel
-//    combines into powers of xt (binomially, in FP64).  |d| is small on a wide
-//    frame, so the higher powers need few bits to add nothing above FP32
-//    rounding: at the narrowest frame taken (FIT_WIDE_MIN columns) |d| <=
-//    2^-6.6, d^2 <= 2^-13, d^3 <= 2^-19, and d^4 is replaced by m^2 d^2 - m^4/8
-//    (m the largest |d|; error m^4/8 <= 2^-29).
-// 2. Split operands.  With s = sqrt(w) c' a power's moment is sum d^a s s^T.
-//    s = h + m + l in bf16 (residual 2^-27 s); power 0 takes the six products
-//    h h, h m, m h, h l, l h, m m (dropped terms 2^-26: below the 2^-24 of an
-//    FP32 product); powers 1 and 2 take d^a s = h_a + m_a and h h_a + h m_a +
-//    m h_a (2^-17 of a term that is 2^-6.6 and 2^-13 of power 0); power 3
-//    takes h h_3.  Products are exact in FP32 and summed in FP32 over 64 pixels, as
-//    before.  A diagonal block's m h and l h are the transposes of h m and h l
-//    (one product each, doubled; the block is symmetrised at the end).
+//    combines into powers of xt (binomially, in FP64).  A solve may cover a
+//    single strip (a narrow tile, or a frame whose other columns are masked):
+//    about that strip's centre every power of d is a diagonal of the system, so
+//    each is held to FP32 accuracy relative to itself, however small |d| is.
+// 2. Split operands.  With s = sqrt(w) c', u = d s and v = d^2 s the moments of
+//    powers 0..4 are s s^T, s u^T, u u^T, u v^T and v v^T.  Each vector is split
+//    into h + m + l in bf16 (residual 2^-27) and a product takes h h, h m, m h,
+//    h l, l h and m m (dropped terms 2^-26: below the 2^-24 of an FP32 product).
+//    Products are exact in FP32 and summed in FP32 over 64 pixels, as before.
 //
-// The right-hand side is summed from the same s: FP32 products over 4 pixels,
-// then FP64 per lane across rows.
+// The right-hand side is summed from the same s, about the strip's centre too:
+// FP32 products over 4 pixels, then FP64 per lane across rows.
 //
 // Waves and pipeline: 8 convolution waves (fit_conv8) write row y's c at step
 // n; the 8 MFMA waves split it (4 basis rows each, a lane per row and 4
@@ -30,27 +26,29 @@
 // barrier per step.  Of the two MFMA waves of a SIMD one multiplies first and
 // the other splits first, so that matrix and vector work meet.
 //
-// Full frame, D = 2, h = 10: 7.46 -> 4.95 ms against the FP32 form, the
-// difference image as far from the 64-bit one as before (9.0e-6 and 9.2e-6
-// relative).  Narrower frames keep the FP32 form: their |d| would need more
-// products, and the frame's 2 D + 1 powers cost them less than the solve.
+// What bounds it: VALU issue (filters, splits, FP64 sums) and, beside it, the
+// products.  Full frame, 21 x 21: degree 2 7.42 -> 6.26 ms against the FP32 form,
+// degree 1 6.16 -> 4.57; the difference image as far from the 64-bit one as
+// before (9.1e-6 relative).  Tiles of 64 to 409 columns at the centre of a 6144
+// x 140 frame: difference 1.2e-5 to 1.1e-4 sigma RMS from the 64-bit solution's,
+// 7.3e-5 to 2.7e-2 with the FP32 form (its powers are those of the frame's
+// coordinate).  Three products for powers 1 to 4 (5.35 ms) leave such tiles'
+// systems indefinite.
 #pragma once
 #include "fit_accum8.h"
 
 namespace argus_fit {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 template <int D, int HH>
 struct FitWideLds {
     using Base = FitLds8<D, HH, false>;
     static constexpr int CKB = SW + 8;                   // row stride of a table (16-byte rows)
-    static constexpr int NJ = D == 1 ? 3 : 4;            // powers of d
-    // tables of one buffer: h, m, l; h1, m1; h2, m2; h3
-    static constexpr int NTAB = D == 1 ? 7 : 8;
+    // tables of one buffer: h, m, l of s, of d s and, for D = 2, of d^2 s
+    static constexpr int NTAB = 3 * (D + 1);
     static constexpr int TAB = 32 * CKB;                 // bf16 values of a table
-    static constexpr int NF = D == 1 ? 6 : 14;           // (power of d, power of yt) moments
+    static constexpr int NF = FitShape<D>::NQ;           // (power of d, power of yt) moments
     static constexpr size_t base = (Base::bytes(8) + 15) & ~(size_t)15;
     static constexpr size_t bytes() {
         constexpr size_t t = base + (size_t)2 * NTAB * TAB * 2;
@@ -62,18 +60,25 @@ struct FitWideLds {
     }
 };
 
-// Tasks (power of d, block pair) of MFMA wave MW: at most two.  The loads are
-// within 14..20 products per SIMD (waves MW and MW + 4 share one).
+// Tasks (power of d, block pair) of MFMA wave MW: at most two, of 12 products
+// each, or 8 for a diagonal block of an even power (waves MW and MW + 4 share a
+// SIMD: 40, 40, 40 and 36 of D = 2's 156 products, 24, 20, 24 and 24 of D = 1's
+// 92).  A high power, with few sums, goes with a low one.
 struct WideTask { int a, bp; };
 template <int D>
 __host__ __device__ constexpr WideTask wide_task(int mw, int i) {
-    constexpr WideTask t2[8][2] = {{{0, 1}, {-1, 0}}, {{0, 0}, {-1, 0}}, {{0, 2}, {-1, 0}},
-                                   {{1, 0}, {3, 0}},  {{1, 2}, {3, 2}},  {{1, 1}, {3, 1}},
-                                   {{2, 0}, {2, 1}},  {{2, 2}, {-1, 0}}};
-    constexpr WideTask t1[8][2] = {{{0, 1}, {-1, 0}}, {{0, 0}, {-1, 0}}, {{0, 2}, {-1, 0}},
-                                   {{1, 0}, {-1, 0}}, {{1, 2}, {-1, 0}}, {{1, 1}, {-1, 0}},
-                                   {{2, 0}, {2, 2}},  {{2, 1}, {-1, 0}}};
+    constexpr WideTask t2[8][2] = {{{0, 0}, {4, 0}}, {{0, 2}, {4, 2}}, {{0, 1}, {4, 1}},
+                                   {{1, 0}, {3, 0}}, {{1, 1}, {3, 1}}, {{1, 2}, {3, 2}},
+                                   {{2, 0}, {2, 2}}, {{2, 1}, {-1, 0}}};
+    constexpr WideTask t1[8][2] = {{{0, 0}, {-1, 0}}, {{0, 2}, {-1, 0}}, {{0, 1}, {-1, 0}},
+                                   {{1, 0}, {-1, 0}}, {{2, 0}, {2, 2}}, {{1, 1}, {-1, 0}},
+                                   {{1, 2}, {-1, 0}}, {{2, 1}, {-1, 0}}};
     return D == 1 ? t1[mw][i] : t2[mw][i];
+}
+
+// xt at the centre of the strip whose first column is sx0
+__device__ __forceinline__ double wide_centre(const FitArgs &a, int sx0) {
+    return ((double)sx0 + 31.5) * a.sx - 1.0;
 }
 
 __device__ __forceinline__ bf16x4 to_bf16(const float (&v)[4]) {
@@ -122,47 +127,52 @@ __device__ void fit_wide_mfma(const FitArgs &a, float *lds, int sx0, int ry0, in
     auto frag = [&](int buf, int t, int half, int s) {
         return *(const bf16x8 *)(L::tab(lds, buf, t) + (16 * half + col) * CKB + 32 * s + 8 * pk);
     };
-    // the moments of one task over a row's 64 pixels; power 0: h h in acc, the
-    // smaller products in cross
-    auto task = [&](auto ta, auto tb, int buf, floatx4 &acc, floatx4 &cross) {
+    // one task: the moments over a row's 64 pixels, h h in acc, the smaller
+    // products in cross (in one sum, the roundings of equal pixels add up), and
+    // their yt powers into the FP64 sums
+    auto task = [&](auto ta, auto tb, double (&F)[NB][4], int buf, const double *ypw) {
         constexpr int A = decltype(ta)::value, BP = decltype(tb)::value;
         constexpr int ra = BP == 2 ? 1 : 0, rb = BP == 0 ? 0 : 1;
-        acc = cross = floatx4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (A == 0) {
+        constexpr int va = 3 * (A / 2), vb = 3 * (A - A / 2);     // first tables of the two vectors
+        constexpr bool SAME = ra == rb && va == vb;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f}, cross = acc;
+#define ARGUS_MM(X, Y, C) C = __builtin_amdgcn_mfma_f32_16x16x32_bf16(X, Y, C, 0, 0, 0);
+        if constexpr (SAME) {
+            // m h and l h are the transposes of h m and h l (the block is
+            // symmetrised at the end): cross is half their sum with m m
+            bf16x8 h[SW / 32], m[SW / 32], l[SW / 32];
 #pragma unroll
             for (int s = 0; s < SW / 32; ++s) {
-                const bf16x8 h0 = frag(buf, 0, ra, s), m0 = frag(buf, 1, ra, s), l0 = frag(buf, 2, ra, s);
-                const bf16x8 h1 = ra == rb ? h0 : frag(buf, 0, rb, s);
-                const bf16x8 m1 = ra == rb ? m0 : frag(buf, 1, rb, s);
-                const bf16x8 l1 = ra == rb ? l0 : frag(buf, 2, rb, s);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, h1, acc, 0, 0, 0);
-                cross = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, l1, cross, 0, 0, 0);
-                cross = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l0, h1, cross, 0, 0, 0);
-                cross = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m0, m1, cross, 0, 0, 0);
-                cross = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, m1, cross, 0, 0, 0);
-                cross = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m0, h1, cross, 0, 0, 0);
+                h[s] = frag(buf, va, ra, s);
+                m[s] = frag(buf, va + 1, ra, s);
+                l[s] = frag(buf, va + 2, ra, s);
+                ARGUS_MM(m[s], m[s], cross)
+                ARGUS_MM(h[s], h[s], acc)
             }
-        } else if constexpr (A == 3) {
 #pragma unroll
-            for (int s = 0; s < SW / 32; ++s)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(buf, 0, ra, s), frag(buf, 7, rb, s),
-                                                              acc, 0, 0, 0);
+            for (int r = 0; r < 4; ++r) cross[r] *= 0.5f;
+#pragma unroll
+            for (int s = 0; s < SW / 32; ++s) {
+                ARGUS_MM(h[s], l[s], cross)
+                ARGUS_MM(h[s], m[s], cross)
+            }
         } else {
 #pragma unroll
             for (int s = 0; s < SW / 32; ++s) {
-                const bf16x8 h = frag(buf, 0, ra, s), m = frag(buf, 1, ra, s);
-                const bf16x8 ha = frag(buf, 1 + 2 * A, rb, s), ma = frag(buf, 2 + 2 * A, rb, s);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h, ma, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, ha, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h, ha, acc, 0, 0, 0);
+                const bf16x8 h0 = frag(buf, va, ra, s), m0 = frag(buf, va + 1, ra, s), l0 = frag(buf, va + 2, ra, s);
+                const bf16x8 h1 = frag(buf, vb, rb, s), m1 = frag(buf, vb + 1, rb, s), l1 = frag(buf, vb + 2, rb, s);
+                ARGUS_MM(h0, h1, acc)
+                ARGUS_MM(h0, l1, cross)
+                ARGUS_MM(l0, h1, cross)
+                ARGUS_MM(m0, m1, cross)
+                ARGUS_MM(h0, m1, cross)
+                ARGUS_MM(m0, h1, cross)
             }
         }
-    };
-    auto flush = [&](auto ta, double (&F)[NB][4], floatx4 acc, floatx4 cross, const double *ypw) {
-        constexpr int A = decltype(ta)::value;
+#undef ARGUS_MM
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const double v = A == 0 ? (double)acc[r] + (double)cross[r] : (double)acc[r];
+            const double v = (double)acc[r] + (SAME ? 2.0 : 1.0) * (double)cross[r];
 #pragma unroll
             for (int b = 0; b <= 2 * D - A; ++b) F[b][r] += ypw[b] * v;
         }
@@ -170,17 +180,9 @@ __device__ void fit_wide_mfma(const FitArgs &a, float *lds, int sx0, int ry0, in
     auto multiply = [&](int y, int buf) {
         double ypw[NB];
         ypowers(y, ypw);
-        using A0 = std::integral_constant<int, T0.a>;
-        floatx4 c0, x0, c1, x1;
-        task(A0{}, std::integral_constant<int, T0.bp>{}, buf, c0, x0);
-        if constexpr (T1.a >= 0) {
-            using A1 = std::integral_constant<int, T1.a>;
-            task(A1{}, std::integral_constant<int, T1.bp>{}, buf, c1, x1);
-            flush(A0{}, F0, c0, x0, ypw);
-            flush(A1{}, F1, c1, x1, ypw);
-        } else {
-            flush(A0{}, F0, c0, x0, ypw);
-        }
+        task(std::integral_constant<int, T0.a>{}, std::integral_constant<int, T0.bp>{}, F0, buf, ypw);
+        if constexpr (T1.a >= 0)
+            task(std::integral_constant<int, T1.a>{}, std::integral_constant<int, T1.bp>{}, F1, buf, ypw);
     };
     // s = sqrt(w) c' of this lane's row and pixels, its tables, and the
     // right-hand side's products
@@ -200,31 +202,23 @@ __device__ void fit_wide_mfma(const FitArgs &a, float *lds, int sx0, int ry0, in
             for (int b = 0; b <= D; ++b)
                 if (e + b <= D) RF[qidx(e, b, D)] += ypw[b] * r;
         }
-        float u[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) u[i] = s[i] * dl[i];
         auto put = [&](int t, bf16x4 v) { *(bf16x4 *)(L::tab(lds, tb, t) + k * CKB + p4) = v; };
-        const bf16x4 h = to_bf16(s);
-        put(0, h);
-        less(s, h);
-        const bf16x4 m = to_bf16(s);
-        put(1, m);
-        less(s, m);
-        put(2, to_bf16(s));
 #pragma unroll
-        for (int j = 1; j < 3; ++j) {
+        for (int j = 0; j <= D; ++j) {                   // s, d s, d^2 s
             float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = u[i];
-            const bf16x4 hj = to_bf16(v);
-            put(1 + 2 * j, hj);
-            less(v, hj);
-            put(2 + 2 * j, to_bf16(v));
-            if (j == 1 || D == 2)
+            for (int i = 0; i < 4; ++i) v[i] = s[i];
+            const bf16x4 h = to_bf16(v);
+            put(3 * j, h);
+            less(v, h);
+            const bf16x4 m = to_bf16(v);
+            put(3 * j + 1, m);
+            less(v, m);
+            put(3 * j + 2, to_bf16(v));
+            if (j < D)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) u[i] *= dl[i];
+                for (int i = 0; i < 4; ++i) s[i] *= dl[i];
         }
-        if constexpr (D == 2) put(7, to_bf16(u));
     };
 
     const int ystart = ry0 - HH, yend = active ? ry1 + HH : ystart;
@@ -242,13 +236,20 @@ __device__ void fit_wide_mfma(const FitArgs &a, float *lds, int sx0, int ry0, in
         if (!SPLIT_FIRST && sp) split(yy - 1 - HH, buf ^ 1, buf);
         __syncthreads();
     }
-    // right-hand side: the 16 lanes of a basis row
+    // right-hand side: the 16 lanes of a basis row; powers of xt as below
 #pragma unroll
-    for (int i = 0; i < S::NR; ++i) {
-        double r = RF[i];
-        for (int off = 8; off > 0; off >>= 1) r += __shfl_xor(r, off);
-        if (col == 0) part[(size_t)S::NQ * 768 + i * 32 + k] = r;
-    }
+    for (int i = 0; i < S::NR; ++i)
+        for (int off = 8; off > 0; off >>= 1) RF[i] += __shfl_xor(RF[i], off);
+    const double x0 = wide_centre(a, sx0);
+#pragma unroll
+    for (int p = 0; p <= D; ++p)
+#pragma unroll
+        for (int b = 0; b <= D - p; ++b) {
+            double v = RF[qidx(p, b, D)];
+            if (p >= 1) v += p * x0 * RF[qidx(p - 1, b, D)];
+            if (p == 2) v += x0 * x0 * RF[qidx(0, b, D)];
+            if (col == 0) part[(size_t)S::NQ * 768 + qidx(p, b, D) * 32 + k] = v;
+        }
     // the moments in powers of d, for the whole workgroup to combine
     double *fb = (double *)lds;
     auto out = [&](WideTask t, const double (&F)[NB][4]) {
@@ -314,38 +315,34 @@ __global__ __launch_bounds__(1024) void fit_wide_kernel(FitArgs a) {
         if (lane == 0) part[(size_t)S::NQ * 768 + S::NR * 32] = c;
     }
     __syncthreads();
-    // powers of xt = x0 + d: xt^p = sum_j C(p, j) x0^(p - j) d^j, with d^4 by
-    // m^2 d^2 - m^4 / 8; diagonal blocks symmetrised
+    // powers of xt = x0 + d: xt^p = sum_j C(p, j) x0^(p - j) d^j; diagonal
+    // blocks symmetrised
     const double *fb = (const double *)lds;
-    const double x0 = ((double)sx0 + 31.5) * a.sx - 1.0;
-    const double mm = (31.5 * a.sx) * (31.5 * a.sx);
-    constexpr double bin[5][4] = {{1, 0, 0, 0}, {1, 1, 0, 0}, {1, 2, 1, 0}, {1, 3, 3, 1}, {1, 4, 6, 4}};
+    const double x0 = wide_centre(a, sx0);
+    constexpr double bin[5][5] = {{1, 0, 0, 0, 0}, {1, 1, 0, 0, 0}, {1, 2, 1, 0, 0}, {1, 3, 3, 1, 0}, {1, 4, 6, 4, 1}};
     for (int i = tid; i < 768; i += 1024) {
         const int bp = i >> 8, r = (i >> 4) & 15, c = i & 15;
         const int it = bp == 1 ? i : (bp << 8) + c * 16 + r;
-        double F[L::NJ][2 * D + 1];
+        double F[2 * D + 1][2 * D + 1];
 #pragma unroll
-        for (int j = 0; j < L::NJ; ++j)
+        for (int j = 0; j <= 2 * D; ++j)
 #pragma unroll
-            for (int b = 0; b <= 2 * D; ++b)
-                if (b <= 2 * D - j) {
-                    const double *f = fb + (size_t)qidx(j, b, 2 * D) * 768;
-                    F[j][b] = 0.5 * (f[i] + f[it]);
-                }
+            for (int b = 0; b <= 2 * D - j; ++b) {
+                const double *f = fb + (size_t)qidx(j, b, 2 * D) * 768;
+                F[j][b] = 0.5 * (f[i] + f[it]);
+            }
 #pragma unroll
         for (int p = 0; p <= 2 * D; ++p)
 #pragma unroll
-            for (int b = 0; b <= 2 * D; ++b)
-                if (p + b <= 2 * D) {
-                    double v = 0.0, xp = 1.0;      // x0^(p - j) from j = p down
+            for (int b = 0; b <= 2 * D - p; ++b) {
+                double v = 0.0, xp = 1.0;      // x0^(p - j) from j = p down
 #pragma unroll
-                    for (int j = p; j >= 0; --j) {
-                        if (j < L::NJ) v += bin[p][j] * xp * F[j][b];
-                        xp *= x0;
-                    }
-                    if (p == 4) v += mm * F[2][b] - (mm * mm / 8.0) * F[0][b];
-                    part[(size_t)qidx(p, b, 2 * D) * 768 + i] = v;
+                for (int j = p; j >= 0; --j) {
+                    v += bin[p][j] * xp * F[j][b];
+                    xp *= x0;
                 }
+                part[(size_t)qidx(p, b, 2 * D) * 768 + i] = v;
+            }
     }
 }
 

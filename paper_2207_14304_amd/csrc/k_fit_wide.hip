@@ -18,12 +18,8 @@ int fit_accum_launch_wide(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, d
     ARGUS_FH(DD, 1) ARGUS_FH(DD, 2) ARGUS_FH(DD, 3) ARGUS_FH(DD, 4) ARGUS_FH(DD, 5)          \
     ARGUS_FH(DD, 6) ARGUS_FH(DD, 7) ARGUS_FH(DD, 8) ARGUS_FH(DD, 9) ARGUS_FH(DD, 10)         \
     ARGUS_FH(DD, 11) ARGUS_FH(DD, 12) ARGUS_FH(DD, 13) ARGUS_FH(DD, 14) ARGUS_FH(DD, 15)
-#ifdef ARGUS_PROBE
-    ARGUS_FH(2, 10) ARGUS_FH(2, 7) ARGUS_FH(1, 7)
-#else
     ARGUS_FD(1)
     ARGUS_FD(2)
-#endif
 #undef ARGUS_FD
 #undef ARGUS_FH
     if (!ok) return argus_fail(ctx, ARGUS_ESHAPE, "unsupported degree %d / half width %d", D, fa.h);
