@@ -15,7 +15,7 @@
 // The transforms move far more bytes than they compute, so the work is three
 // passes over one 16-byte plane per tile (58 B read and 48 B written per
 // tile pixel with the inputs and outputs):
-//   rows     N + i R (two real images, one complex transform) row by row; the
+//   rows     N + i g R (two real images, one complex transform) row by row; the
 //            spectra go out transposed, [k_x][y];
 //   columns  k_x and -k_x together in one workgroup: forward, N^ and R^ from
 //            the symmetric and antisymmetric parts, D^ + i S^ (D and S are
@@ -23,6 +23,10 @@
 //            a workgroup keeps its columns' filter values in registers and
 //            takes many tiles;
 //   output   inverse rows, scaling, masks.
+// Two images in one transform share its rounding, so they are brought to one
+// scale by powers of two first: R by g = 2^k next to F_n / F_r (the images may
+// be in any units), S by the one next to 1 / sqrt(sum P_D^2) (the PSFs may have
+// any sums; their own transforms are kept apart).
 // A length-L transform is L / 8 threads with 8 values each in registers and
 // radix-8 steps (one radix-4 or -2 step where 3 does not divide log2 L)
 // exchanged through LDS.  280 tiles of 512^2: 10.9 -> 1.69 ms, against two
@@ -195,6 +199,7 @@ struct RowArgs {
     const cplx *tw;
     cplx *Z;                           // [n][k_x][y]
     uint64_t *bits;                    // [n][y][L / 64]: flagged along x within rad
+    double g;                          // scale of R
 };
 
 // OR of the bits of the word `c` and its neighbours within rad (< 64) places
@@ -210,8 +215,8 @@ __device__ __forceinline__ uint64_t dilate_bits(uint64_t p, uint64_t c, uint64_t
     return (uint64_t)(up >> 64) | (uint64_t)dn;
 }
 
-// Row transforms of N + i R (PSF: of the two stamps wrapped onto the tile,
-// centre at the origin).
+// Row transforms of N + i g R (PSF: of the stamps N and R, a plane each, wrapped
+// onto the tile, centre at the origin).
 template <int LG, bool PSF>
 __global__ __launch_bounds__(512) void zogy_rows_kernel(RowArgs a) {
     using F = Fft<LG>;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(512) void zogy_rows_kernel(RowArgs a) {
             const int x = u + r * T, du = x <= L / 2 ? x : x - L;
             const bool in = dv >= -a.r && dv <= a.r && du >= -a.r && du <= a.r;
             const int i = (dv + a.r) * K + du + a.r;
-            v[r] = in ? make_double2(a.N[i], a.R[i]) : make_double2(0.0, 0.0);
+            v[r] = make_double2(in ? (double)(t == 0 ? a.N : a.R)[i] : 0.0, 0.0);
         }
     } else {
         const int X0 = a.org[2 * t], Y = a.org[2 * t + 1] + y;
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(512) void zogy_rows_kernel(RowArgs a) {
         }
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            v[r] = bad[r] ? make_double2(0.0, 0.0) : make_double2(vn[r], vr[r]);
+            v[r] = bad[r] ? make_double2(0.0, 0.0) : make_double2(vn[r], a.g * vr[r]);
             const uint64_t b = __ballot(bad[r]);
             // the T bits of this row's pixels [r T, (r + 1) T)
             if constexpr (T >= 64) {
@@ -283,8 +288,8 @@ struct ZCoef {
     double Fn, Fr, sn2, sr2, FD;
 };
 
-// Filter values per frequency, [k_x][k_y]: D^ = A N^ - B R^ with A = F_r P_r^ /
-// den and B = F_n P_n^ / den, conj(P_D^) = q conj(A B) with q = den / F_D.
+// Filter values per frequency, [k_x][k_y]: D^ = A N^ - B (g R)^ with A = F_r P_r^
+// / den and B = F_n P_n^ / (g den), conj(P_D^) = q conj(A B) with q = g den / F_D.
 struct Filter {
     cplx *A, *B;
     double *q;
@@ -323,29 +328,37 @@ __device__ __forceinline__ void split(cplx v, cplx m, cplx &X, cplx &Y) {
     Y = make_double2(0.5 * (v.y + m.y), 0.5 * (m.x - v.x));
 }
 
-// Filter values from the PSF plane, and each workgroup's sum of |P_D^|^2.
+// The power of two next to 1 / sqrt(pd2), the scale that S is carried at.
+__device__ __forceinline__ double score_scale(double pd2) {
+    return pd2 > 0.0 && pd2 < __builtin_inf() ? ldexp(1.0, -(ilogb(pd2) >> 1)) : 1.0;
+}
+
+// Filter values from the PSF planes, and each workgroup's sum of |P_D^|^2.
 template <int LG>
 __global__ __launch_bounds__(256) void zogy_filter_kernel(const cplx *Z, const cplx *tw, ZCoef c,
-                                                          Filter fl, double *part) {
+                                                          double g, Filter fl, double *part) {
     using F = Fft<LG>;
     extern __shared__ cplx sm[];
     __shared__ double red[4];
     const Column<LG> col(sm);
-    cplx v[8], m[8];
+    const cplx *z = Z + (size_t)col.kx * F::L + col.u;
+    cplx vn[8], vr[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = Z[(size_t)col.kx * F::L + col.u + r * F::T];
-    fft<LG, false>(v, col.u, tw, col.own);
-    col.mirrored(v, m);
+    for (int r = 0; r < 8; ++r) {
+        vn[r] = z[r * F::T];
+        vr[r] = z[(size_t)F::L * F::L + r * F::T];
+    }
+    fft<LG, false>(vn, col.u, tw, col.own);
+    fft<LG, false>(vr, col.u, tw, col.own);
     double s = 0.0;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        cplx Pn, Pr;
-        split(v[r], m[r], Pn, Pr);
+        const cplx Pn = vn[r], Pr = vr[r];
         const double an = Pn.x * Pn.x + Pn.y * Pn.y, ar = Pr.x * Pr.x + Pr.y * Pr.y;
         const double den = sqrt(c.sn2 * c.Fr * c.Fr * ar + c.sr2 * c.Fn * c.Fn * an);
-        const double ia = den > 0.0 ? c.Fr / den : 0.0, ib = den > 0.0 ? c.Fn / den : 0.0;
+        const double ia = den > 0.0 ? c.Fr / den : 0.0, ib = den > 0.0 ? c.Fn / den / g : 0.0;
         const cplx A = make_double2(ia * Pr.x, ia * Pr.y), B = make_double2(ib * Pn.x, ib * Pn.y);
-        const double q = den / c.FD;
+        const double q = g * (den / c.FD);
         const size_t i = (size_t)col.kx * F::L + col.u + r * F::T;
         fl.A[i] = A;
         fl.B[i] = B;
@@ -371,7 +384,7 @@ __global__ __launch_bounds__(64) void zogy_pd2_kernel(const double *part, int n,
 // Columns of the tiles [blockIdx.y per, ...): forward, filter, inverse.
 template <int LG>
 __global__ __launch_bounds__(256) void zogy_columns_kernel(cplx *Z, const cplx *tw, Filter fl,
-                                                           int n, int per) {
+                                                           const double *pd2, int n, int per) {
     using F = Fft<LG>;
     constexpr int L = F::L, T = F::T;
     extern __shared__ cplx sm[];
@@ -379,11 +392,12 @@ __global__ __launch_bounds__(256) void zogy_columns_kernel(cplx *Z, const cplx *
     cplx A[8], B[8];
     double q[8];
     const size_t o = (size_t)col.kx * L + col.u;
+    const double sc = score_scale(*pd2);
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         A[r] = fl.A[o + r * T];
         B[r] = fl.B[o + r * T];
-        q[r] = fl.q[o + r * T];
+        q[r] = sc * fl.q[o + r * T];
     }
     const int t1 = min((int)(blockIdx.y + 1) * per, n);
     for (int t = blockIdx.y * per; t < t1; ++t) {
@@ -447,7 +461,7 @@ __global__ __launch_bounds__(512) void zogy_out_kernel(OutArgs a) {
     F::sync();
     fft<LG, true>(v, u, a.tw, row);
     const double inv = 1.0 / ((double)L * L), pd2 = *a.pd2;
-    const double is = 1.0 / sqrt(pd2), ifl = 1.0 / (a.FD * pd2);
+    const double sc = score_scale(pd2), is = 1.0 / sqrt(pd2) / sc, ifl = 1.0 / (a.FD * pd2) / sc;
     const bool yedge = y < a.r || y >= L - a.r;
     const size_t o = ((size_t)t * L + y) * L;
 #pragma unroll
@@ -496,15 +510,15 @@ int zogy_run(argus_ctx *ctx, ZCall &z) {
     p.N = z.psf_n;
     p.R = z.psf_r;
     p.Z = z.psf;
-    hipLaunchKernelGGL((zogy_rows_kernel<LG, true>), dim3(L / F::NF), dim3(512), row_lds, st, p);
+    hipLaunchKernelGGL((zogy_rows_kernel<LG, true>), dim3(2 * (L / F::NF)), dim3(512), row_lds, st, p);
     hipLaunchKernelGGL(zogy_filter_kernel<LG>, dim3(pairs), dim3(256), col_lds, st,
-                       (const cplx *)z.psf, (const cplx *)z.tw, z.c, z.fl, z.part);
+                       (const cplx *)z.psf, (const cplx *)z.tw, z.c, z.rows.g, z.fl, z.part);
     hipLaunchKernelGGL(zogy_pd2_kernel, dim3(1), dim3(64), 0, st, (const double *)z.part, pairs,
                        1.0 / ((double)L * L), z.pd2);
     hipLaunchKernelGGL((zogy_rows_kernel<LG, false>), dim3(z.n * (L / F::NF)), dim3(512), row_lds, st,
                        z.rows);
     hipLaunchKernelGGL(zogy_columns_kernel<LG>, dim3(pairs, (z.n + per - 1) / per), dim3(256), col_lds,
-                       st, z.Z, (const cplx *)z.tw, z.fl, z.n, per);
+                       st, z.Z, (const cplx *)z.tw, z.fl, (const double *)z.pd2, z.n, per);
     hipLaunchKernelGGL(zogy_out_kernel<LG>, dim3(z.n * (L / F::NF)), dim3(512), row_lds, st, z.out);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     argus_time_end(ctx, "zogy");
@@ -518,10 +532,10 @@ int launch_zogy(argus_ctx *ctx, argus_dims d, const float *N, const uint8_t *mn,
                 const float *psf_r, int r, double Fn, double Fr, double sn, double sr, float *D,
                 float *snr, float *flux, uint8_t *mask, double *pd2_out) {
     const size_t LL = (size_t)L * L;
-    // workspace: a spectrum plane per tile, the PSF plane, the filter values,
+    // workspace: a spectrum plane per tile, the PSF planes, the filter values,
     // twiddles, the flag bits, partial sums and sum P_D^2
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t o_psf = al(n * LL * sizeof(cplx)), o_a = o_psf + al(LL * sizeof(cplx)),
+    const size_t o_psf = al(n * LL * sizeof(cplx)), o_a = o_psf + al(2 * LL * sizeof(cplx)),
                  o_b = o_a + al(LL * sizeof(cplx)), o_q = o_b + al(LL * sizeof(cplx)),
                  o_tw = o_q + al(LL * sizeof(double)), o_bits = o_tw + al(L * sizeof(cplx)),
                  o_part = o_bits + al(n * LL / 8), o_pd2 = o_part + al(L * sizeof(double)),
@@ -542,7 +556,10 @@ int launch_zogy(argus_ctx *ctx, argus_dims d, const float *N, const uint8_t *mn,
     z.c.Fn = Fn; z.c.Fr = Fr; z.c.sn2 = sn * sn; z.c.sr2 = sr * sr;
     z.c.FD = Fn * Fr / sqrt(z.c.sn2 * Fr * Fr + z.c.sr2 * Fn * Fn);
     uint64_t *bits = (uint64_t *)(ws + o_bits);
-    z.rows = RowArgs{N, R, mn, mr, origins, d.pitch, d.width, d.height, r, 2 * r, z.tw, z.Z, bits};
+    // (an FP32 image times 2^+-800 is a normal FP64 number)
+    const int k = ilogb(Fn) - ilogb(Fr);
+    const double g = ldexp(1.0, k < -800 ? -800 : k > 800 ? 800 : k);
+    z.rows = RowArgs{N, R, mn, mr, origins, d.pitch, d.width, d.height, r, 2 * r, z.tw, z.Z, bits, g};
     z.out = OutArgs{z.Z, z.tw, bits, z.pd2, D, snr, flux, mask, z.c.FD, r, 2 * r};
     switch (L) {
         case 64: return zogy_run<6>(ctx, z);
