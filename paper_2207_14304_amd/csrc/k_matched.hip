@@ -32,43 +32,45 @@ struct MatchedArgs {
     int W, H, n, bx;                   // bx: blocks along x
 };
 
-template <int R>
+template <int R, int TX, int TY, int PX>
 struct MLds {
     static constexpr int K = 2 * R + 1;
-    static constexpr int TH = BH + 2 * R;
-    static constexpr int TWr = BW + 2 * R;
+    static constexpr int TH = TY + 2 * R;
+    static constexpr int TWr = TX + 2 * R;
     static constexpr int TW = (TWr + 3) & ~3;
+    static constexpr int NT = TX / PX * TY;              // threads
     static constexpr size_t bytes = (size_t)(2 * TH * TW + 2 * K * K + 8) * 4;
 };
 
-template <int R>
-__global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
-    using L = MLds<R>;
-    constexpr int K = L::K, TH = L::TH, TW = L::TW, TWr = L::TWr;
-    extern __shared__ __align__(16) float lds[];
+// Sums of a TX x TY tile, PX consecutive pixels of a row per thread: s the
+// scores of the pixels from (lx0, ly) on, v their variances.
+template <int R, int TX, int TY, int PX>
+__device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, int bx0, int by0,
+                                             int ly, int lx0, double (&s)[PX], double (&v)[PX]) {
+    using L = MLds<R, TX, TY, PX>;
+    constexpr int K = L::K, TH = L::TH, TW = L::TW, TWr = L::TWr, NT = L::NT;
     float *At = lds;                   // [TH][TW] M / V
     float *Bt = At + TH * TW;          // [TH][TW] 1 / V
     float *Pt = Bt + TH * TW;          // [K*K][2] F p, F^2 p^2
     const int tid = threadIdx.x;
-    const int bx0 = (blockIdx.x % a.bx) * BW, by0 = (blockIdx.x / a.bx) * BH;
     const int64_t P = a.pitch;
-    const int ly = tid / (BW / PXT), lx0 = (tid % (BW / PXT)) * PXT;
     // FP32 sums along a PSF row, FP64 across rows and images
-    double s[PXT], v[PXT];
 #pragma unroll
-    for (int i = 0; i < PXT; ++i) { s[i] = 0.0; v[i] = 0.0; }
+    for (int i = 0; i < PX; ++i) { s[i] = 0.0; v[i] = 0.0; }
+#pragma unroll 1
     for (int j = 0; j < a.n; ++j) {
         __syncthreads();                                  // the previous image's reads are done
         const float *cal = a.cal[j], *var = a.var[j];
         const uint8_t *msk = a.mask[j];
         const BgGrid bg = a.bg[j];
-        constexpr int NE = TH * TWr, NH = (NE + NTHR - 1) / NTHR, NB = 8;
+        constexpr int NE = TH * TWr, NH = (NE + NT - 1) / NT, NB = PX == 8 ? 8 : 4;
+#pragma unroll 1
         for (int j0 = 0; j0 < NH; j0 += NB) {
             float hc[NB], hv[NB];
             uint8_t hm[NB];
 #pragma unroll
             for (int e = 0; e < NB; ++e) {
-                const int i = tid + (j0 + e) * NTHR;
+                const int i = tid + (j0 + e) * NT;
                 const int ii = i < NE ? i : 0;
                 int X = bx0 - R + ii % TWr, Y = by0 - R + ii / TWr;
                 X = X < 0 ? 0 : (X >= a.W ? a.W - 1 : X);
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
             }
 #pragma unroll
             for (int e = 0; e < NB; ++e) {
-                const int i = tid + (j0 + e) * NTHR;
+                const int i = tid + (j0 + e) * NT;
                 if (i < NE) {
                     const int cy = i / TWr, cx = i % TWr;
                     const int X = bx0 - R + cx, Y = by0 - R + cy;
@@ -95,17 +97,18 @@ __global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
         }
         const float *pj = a.psf + (size_t)j * K * K;
         const float F = a.F[j];
-        for (int t = tid; t < K * K; t += NTHR) {
+        for (int t = tid; t < K * K; t += NT) {
             const float p = pj[t];
             Pt[2 * t] = F * p;
             Pt[2 * t + 1] = (F * F) * (p * p);
         }
         __syncthreads();
+#pragma unroll 1
         for (int dv = 0; dv < K; ++dv) {
             // the windows of this PSF row as 16-byte reads (rows are 16-byte
             // aligned; the last read may pass the window by up to three
             // floats, still inside the LDS carve-up)
-            constexpr int NW4 = (PXT + 2 * R + 3) / 4;
+            constexpr int NW4 = (PX + 2 * R + 3) / 4;
             const float4 *ra = (const float4 *)(At + (ly + dv) * TW + lx0);
             const float4 *rb = (const float4 *)(Bt + (ly + dv) * TW + lx0);
             float wa[4 * NW4], wb[4 * NW4];
@@ -115,25 +118,36 @@ __global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
                 wa[4 * q] = x4.x; wa[4 * q + 1] = x4.y; wa[4 * q + 2] = x4.z; wa[4 * q + 3] = x4.w;
                 wb[4 * q] = y4.x; wb[4 * q + 1] = y4.y; wb[4 * q + 2] = y4.z; wb[4 * q + 3] = y4.w;
             }
-            float rs[PXT], rv[PXT];
+            float rs[PX], rv[PX];
 #pragma unroll
-            for (int i = 0; i < PXT; ++i) { rs[i] = 0.f; rv[i] = 0.f; }
+            for (int i = 0; i < PX; ++i) { rs[i] = 0.f; rv[i] = 0.f; }
 #pragma unroll
             for (int du = 0; du < K; ++du) {
                 const float2 pp = *(const float2 *)(Pt + 2 * (dv * K + du));
 #pragma unroll
-                for (int i = 0; i < PXT; ++i) {
+                for (int i = 0; i < PX; ++i) {
                     rs[i] += pp.x * wa[i + du];
                     rv[i] += pp.y * wb[i + du];
                 }
             }
 #pragma unroll
-            for (int i = 0; i < PXT; ++i) {
+            for (int i = 0; i < PX; ++i) {
                 s[i] += (double)rs[i];
                 v[i] += (double)rv[i];
             }
         }
     }
+}
+
+template <int R>
+__global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    const int tid = threadIdx.x;
+    const int bx0 = (blockIdx.x % a.bx) * BW, by0 = (blockIdx.x / a.bx) * BH;
+    const int64_t P = a.pitch;
+    const int ly = tid / (BW / PXT), lx0 = (tid % (BW / PXT)) * PXT;
+    double s[PXT], v[PXT];
+    matched_tile<R, BW, BH, PXT>(a, lds, bx0, by0, ly, lx0, s, v);
     const int Y = by0 + ly;
     if (Y >= a.H) return;
     const int64_t orow = (int64_t)Y * P;
@@ -167,12 +181,17 @@ __global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
 // every fourth PSF row for all 8 blocks of 16 x 16 outputs, and the waves' FP64
 // sums meet in LDS at the end.  0 * non-finite would reach outputs outside the
 // PSF's support, and values of extreme exponent lose their low parts: a tile
-// with such values takes plain loops instead.  4788 x 3194, 5 images, 15 x 15:
-// 1.72 -> 0.91 ms (VALU issue 0.49 and MFMA 0.35 of it, which hardly overlap).
+// with such values takes the FP32 form instead (matched_tile; a frame of nothing
+// else, 1500 x 1000, 3 images: 128 us against 117 with matched_kernel and 83 with
+// the splits).  An infinite variance is only a zero weight, and stays.  4788 x
+// 3194, 5 images, 15 x 15: 1.72 -> 0.93 ms (VALU issue 0.49 and MFMA 0.35 of it,
+// which hardly overlap).
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x1 __attribute__((ext_vector_type(1)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int POSITIVE_FINITE = 0x180;                   // class mask: positive normal or subnormal
 
 template <int R>
 struct XLds {
@@ -266,8 +285,8 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
     };
     auto stage = [&](int j) {
         const BgGrid bg = a.bg[j];
-        // largest magnitudes, and a sum that is NaN after an infinity or NaN
-        float big = 0.f, vbig = 0.f, fin = 0.f;
+        // largest magnitude, and a sum that is NaN after an infinity or NaN
+        float big = 0.f, fin = 0.f;
 #pragma unroll 1
         for (int e = 0; e < L::NIT; ++e) {
             const int i = tid + e * L::NT;
@@ -303,10 +322,13 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
                 }
             }
             const bool yin = Y >= 0 && Y < a.H;
+            float vbig = 0.f, mm[4];
+            uint32_t used = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const bool ok = yin && X + k >= 0 && X + k < a.W &&
-                                ((qm >> (8 * k)) & 0xffu) == 0 && v[k] > 0.f;
+                // (an infinite variance is a zero weight)
+                const bool in = yin && X + k >= 0 && X + k < a.W && ((qm >> (8 * k)) & 0xffu) == 0;
+                const bool ok = in && __builtin_amdgcn_classf(v[k], POSITIVE_FINITE);
                 const float m = c[k] - g[k];
                 // 1 / V by one Newton step, m / V from it by one correction
                 float rv = __builtin_amdgcn_rcpf(v[k]);
@@ -315,8 +337,18 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
                 B[k] = ok ? rv : 0.f;
                 A[k] = ok ? mv : 0.f;
                 big = fmaxf(big, fmaxf(fabsf(A[k]), B[k]));
-                vbig = fmaxf(vbig, ok ? v[k] : 0.f);
+                vbig = fmaxf(vbig, v[k]);
+                if (in) used |= 1u << k;
+                mm[k] = m;
                 fin = fmaf(A[k], 0.f, fmaf(B[k], 0.f, fin));
+            }
+            if (vbig > 1e30f) {
+                // rare: a weight too small for the split, or none under a value
+                // that is not finite
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if ((used >> k) & 1u && v[k] > 1e30f && (v[k] < __builtin_inff() || !(fabsf(mm[k]) < __builtin_inff())))
+                        big = __builtin_inff();
             }
             __bf16 *t = tile + cy * L::RS + cx;
             bf16x4 h, m, l;
@@ -329,7 +361,7 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
             *(bf16x4 *)(t + 4 * L::PL) = m;
             *(bf16x4 *)(t + 5 * L::PL) = l;
         }
-        if (__any(!(big < 1e30f) || vbig > 1e30f || fin != 0.f) && lane == 0) odd = 1;
+        if (__any(!(big < 1e30f) || fin != 0.f) && lane == 0) odd = 1;
         // the image's taps
         const float *pj = a.psf + (size_t)j * L::K * L::K;
         const float F = a.F[j];
@@ -408,33 +440,13 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
         if (a.snr) a.snr[o] = V > 0.0 ? (float)(S / sqrt(V)) : 0.f;
     };
     if (odd) {
-        // plain loops: FP32 sums along a PSF row, FP64 across rows and images
-        for (int i = tid; i < L::TX * L::TY; i += L::NT) {
-            const int X = x0 + i % L::TX, Y = y0 + i / L::TX;
-            if (X >= a.W || Y >= a.H) continue;
-            double S = 0.0, V = 0.0;
-            for (int j = 0; j < a.n; ++j) {
-                const float F = a.F[j];
-                for (int dv = 0; dv < L::K; ++dv) {
-                    const int yy = Y + dv - R;
-                    if (yy < 0 || yy >= a.H) continue;
-                    float rs = 0.f, rv = 0.f;
-                    for (int du = 0; du < L::K; ++du) {
-                        const int xx = X + du - R;
-                        const int64_t o = (int64_t)yy * P + xx;
-                        if (xx < 0 || xx >= a.W || a.mask[j][o] != 0 || !(a.var[j][o] > 0.f)) continue;
-                        const float w = a.var[j][o], p = a.psf[((size_t)j * L::K + dv) * L::K + du];
-                        float m = a.cal[j][o];
-                        if (a.bg[j].grid) m -= bg_at(a.bg[j], xx, yy);
-                        rs += F * p * (m / w);
-                        rv += (F * F) * (p * p) * (1.f / w);
-                    }
-                    S += (double)rs;
-                    V += (double)rv;
-                }
-            }
-            put(X, Y, S, V);
-        }
+        double S4[4], V4[4];
+        const int ly = tid >> 4, lx0 = 4 * (tid & 15);
+        static_assert(L::TX == 64 && MLds<R, L::TX, L::TY, 4>::NT == L::NT, "four pixels a thread");
+        static_assert(MLds<R, L::TX, L::TY, 4>::bytes <= L::bytes, "the FP32 tile fits the planes");
+        matched_tile<R, L::TX, L::TY, 4>(a, (float *)xl, x0, y0, ly, lx0, S4, V4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) put(x0 + lx0 + i, y0 + ly, S4[i], V4[i]);
         return;
     }
     // the four waves' sums of each block, wave b adding block b's, first the
@@ -479,7 +491,7 @@ int matched_mfma_launch(argus_ctx *ctx, MatchedArgs a) {
 
 template <int R>
 int matched_launch(argus_ctx *ctx, const MatchedArgs &a, int nblocks) {
-    const size_t lds = MLds<R>::bytes;
+    const size_t lds = MLds<R, BW, BH, PXT>::bytes;
     ARGUS_HIP_CHECK(ctx, hipFuncSetAttribute((const void *)matched_kernel<R>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(matched_kernel<R>, dim3(nblocks), dim3(NTHR), lds, ctx->stream, a);

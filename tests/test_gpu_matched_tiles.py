@@ -99,3 +99,38 @@ def test_strange_values_stay_in_their_window(ctx, kind):
                                        [p.astype(np.float64) for p in psfs], [1.0, 1.0])
     assert (np.abs(N - oN) - 1e-6 * np.abs(oN))[ok].max() <= 1e-4
     assert np.abs(V[ok] / oV[ok] - 1).max() <= 1e-5
+
+
+@pytest.mark.parametrize("kind", ["units", "infinite variance", "nan", "nan of infinite variance"])
+def test_values_out_of_the_split_range(ctx, kind):
+    """Images in units of 1e-17 (1 / V = 1e31), pixels of infinite variance (a
+    zero weight) and NaN pixels: the outputs of ordinary frames, to the same
+    bars, and NaN in exactly the windows that hold one."""
+    W, H, r, n = 210, 100, 7, 3
+    fr = _frames(W, H, n, 12)
+    rng = np.random.default_rng(3)
+    u = 1.0
+    hit = rng.random((H, W)) < 3e-3
+    hit[:10] = hit[-9:] = False
+    fr[1][2][hit] = 0
+    if kind == "units":
+        u = 1e-17
+        fr = [((c * u).astype(np.float32), (v * u * u).astype(np.float32), m) for c, v, m in fr]
+    elif kind == "infinite variance":
+        fr[1][1][hit] = np.inf
+    else:
+        fr[1][0][hit] = np.nan
+        if kind != "nan":
+            fr[1][1][hit] = np.inf
+    psfs = np.stack([synth.psf_image(r, 2.0)] * n).astype(np.float32)
+    S, V, N = _run(ctx, fr, psfs, r, [1.0] * n)
+    win = np.zeros((H, W), bool)
+    if kind.startswith("nan"):
+        for y, x in zip(*np.nonzero(hit)):
+            win[max(y - r, 0):y + r + 1, max(x - r, 0):x + r + 1] = True
+    assert np.array_equal(np.isnan(S), win) and np.all(np.isfinite(V))
+    zero = [(np.nan_to_num(c.astype(np.float64)) / u, v.astype(np.float64) / u / u, m) for c, v, m in fr]
+    oS, oV, oN = matched.matched_coadd([f[0] for f in zero], [f[1] for f in zero], [f[2] for f in zero],
+                                       [None] * n, [p.astype(np.float64) for p in psfs], [1.0] * n)
+    assert np.abs(V * u * u / oV - 1)[~win].max() <= 1e-5
+    assert (np.abs(N - oN) - 1e-6 * np.abs(oN))[~win].max() <= 1e-4
