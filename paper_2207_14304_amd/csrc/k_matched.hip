@@ -232,7 +232,8 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
     __shared__ __align__(16) int scn[L::COLS];
     __shared__ float srx[L::ROWS];                       // and rows
     __shared__ int srn[L::ROWS];
-    __shared__ int odd;
+    __shared__ uint32_t high;                            // see range()
+    __shared__ uint8_t tapok[ARGUS_MAX_FRAMES], taplow[ARGUS_MAX_FRAMES];
     __bf16 *tile = (__bf16 *)xl;                         // planes: M/V h, m, l; 1/V h, m, l
     __bf16 *taps = tile + 6 * L::PL;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -242,7 +243,8 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
     const int x0 = lb % a.bx * L::TX, y0 = lb / a.bx * L::TY;
     const int64_t P = a.pitch;
     const int half = wv >> 2;                            // 0: score, 1: its variance
-    if (tid == 0) odd = 0;
+    if (tid == 0) high = 0;
+    if (tid < ARGUS_MAX_FRAMES) tapok[tid] = taplow[tid] = 0;
     {
         // (every image's grid has the same cells)
         BgGrid g = a.bg[0];
@@ -361,14 +363,16 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
             *(bf16x4 *)(t + 4 * L::PL) = m;
             *(bf16x4 *)(t + 5 * L::PL) = l;
         }
-        if (__any(!(big < 1e30f) || fin != 0.f) && lane == 0) odd = 1;
         // the image's taps
         const float *pj = a.psf + (size_t)j * L::K * L::K;
         const float F = a.F[j];
+        float tap = 0.f;                                 // largest |F p| (its square for F^2 p^2)
         for (int i = tid; i < L::TP; i += L::NT) {
             const int dv = i / L::TL, t = i % L::TL, du = t - 16 - (L::LEFT - R);
             const float p = du >= 0 && du < L::K ? pj[dv * L::K + du] : 0.f;
             float v1[1] = {F * p}, v2[1] = {(F * F) * (p * p)};
+            tap = fmaxf(tap, fabsf(v1[0]));
+            fin = fmaf(v1[0], 0.f, fin);
             __bf16 sp[2][3];
             bf16x1 h, m, l;
             split3(v1, h, m, l);
@@ -382,7 +386,26 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
                 if (t > 0) d[L::TP + t - 1] = sp[q / 3][q % 3];
             }
         }
+        if (__any(big >= 1e4f || tap >= 4.f || fin != 0.f)) {
+            const uint32_t h = (__any(!(big < 1e36f) || !(tap < 1e15f) || fin != 0.f) ? 1u : 0u) |
+                               (__any(big >= 1e4f) ? 2u : 0u) | (__any(big >= 1e28f) ? 4u : 0u) |
+                               (__any(tap >= 4.f) ? 8u : 0u) | (__any(tap >= 1e4f) ? 16u : 0u);
+            if (lane == 0) atomicOr(&high, h);
+        }
+        if (__any(tap >= 1e-14f)) {
+            if (lane == 0) tapok[j] = 1;
+        } else if (__any(tap > 0.f) && lane == 0) {
+            taplow[j] = 1;
+        }
     };
+    // Whether the sums stay inside the split's range: every value finite, no
+    // product above 1e36 (1/V or M/V below 1e4, 1e28, 1e36 with F^2 p^2 below 1e30,
+    // 1e8, 16), and image j's taps large enough (1e-28, with 1/V at least 1e-30)
+    // that the low parts of all that matter are normal numbers.
+    auto range = [&](int j) {
+        return !(high & 1u) && (high & 18u) != 18u && (high & 12u) != 12u && (tapok[j] || !taplow[j]);
+    };
+    bool ok = true;
     double s[L::NB][4];
 #pragma unroll
     for (int b = 0; b < L::NB; ++b)
@@ -392,7 +415,7 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
     for (int j = 0; j < a.n; ++j) {
         stage(j);
         __syncthreads();
-        if (odd) break;
+        if (!(ok = range(j))) break;
         // T_dv of this lane: rows k = 8 pk + e, column x = col, taps k - x
         const int t0 = 8 * pk - col + 16;
         const __bf16 *tp = taps + half * 6 * L::TP + (t0 & 1) * L::TP + (t0 & ~1);
@@ -439,7 +462,7 @@ __global__ __launch_bounds__(512, 4) void matched_mfma_kernel(MatchedArgs a, int
         a.Var[o] = (float)V;
         if (a.snr) a.snr[o] = V > 0.0 ? (float)(S / sqrt(V)) : 0.f;
     };
-    if (odd) {
+    if (!ok) {
         double S4[4], V4[4];
         const int ly = tid >> 4, lx0 = 4 * (tid & 15);
         static_assert(L::TX == 64 && MLds<R, L::TX, L::TY, 4>::NT == L::NT, "four pixels a thread");

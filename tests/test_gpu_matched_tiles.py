@@ -134,3 +134,20 @@ def test_values_out_of_the_split_range(ctx, kind):
                                        [None] * n, [p.astype(np.float64) for p in psfs], [1.0] * n)
     assert np.abs(V * u * u / oV - 1)[~win].max() <= 1e-5
     assert (np.abs(N - oN) - 1e-6 * np.abs(oN))[~win].max() <= 1e-4
+
+
+@pytest.mark.parametrize("u,F", [(1e-14, 1e-17), (1e-17, 1.0), (1.0, 1e16), (1.0, 3e-14), (3e-18, 1e3)])
+def test_zero_points_and_units(ctx, u, F):
+    """Images in units of u and zero points F: F^2 p^2 down to 1e-36 (no low parts
+    left to split) and up to 1e30, 1/V up to 1e32.  The variances to 1e-5 and the
+    SNR, which no unit changes, to the usual bar."""
+    W, H, r, n = 130, 70, 7, 2
+    fr = [((c * u).astype(np.float32), (v * u * u).astype(np.float32), m) for c, v, m in _frames(W, H, n, 4)]
+    psfs = np.stack([synth.psf_image(r, 2.2)] * n).astype(np.float32)
+    S, V, N = _run(ctx, fr, psfs, r, [F] * n)
+    big = [(c.astype(np.float64) / u, v.astype(np.float64) / u / u, m) for c, v, m in fr]
+    oS, oV, oN = matched.matched_coadd([f[0] for f in big], [f[1] for f in big], [f[2] for f in big],
+                                       [None] * n, [p.astype(np.float64) for p in psfs], [1.0] * n)
+    pos = oV > 0
+    assert np.abs(V[pos].astype(np.float64) / float(np.float32(F)) ** 2 * u * u / oV[pos] - 1).max() <= 1e-5
+    assert (np.abs(N - oN) - 1e-6 * np.abs(oN)).max() <= 1e-4
