@@ -49,6 +49,8 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
                                              int ly, int lx0, double (&s)[PX], double (&v)[PX]) {
     using L = MLds<R, TX, TY, PX>;
     constexpr int K = L::K, TH = L::TH, TW = L::TW, TWr = L::TWr, NT = L::NT;
+    // unrolled, a small PSF's rows run 12 % faster; a large one's spill
+    constexpr bool ROLLED = PX == 4 || R > 4;
     float *At = lds;                   // [TH][TW] M / V
     float *Bt = At + TH * TW;          // [TH][TW] 1 / V
     float *Pt = Bt + TH * TW;          // [K*K][2] F p, F^2 p^2
@@ -57,14 +59,13 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
     // FP32 sums along a PSF row, FP64 across rows and images
 #pragma unroll
     for (int i = 0; i < PX; ++i) { s[i] = 0.0; v[i] = 0.0; }
-#pragma unroll 1
     for (int j = 0; j < a.n; ++j) {
         __syncthreads();                                  // the previous image's reads are done
         const float *cal = a.cal[j], *var = a.var[j];
         const uint8_t *msk = a.mask[j];
         const BgGrid bg = a.bg[j];
         constexpr int NE = TH * TWr, NH = (NE + NT - 1) / NT, NB = PX == 8 ? 8 : 4;
-#pragma unroll 1
+#pragma unroll (ROLLED ? 1 : (NH + NB - 1) / NB)
         for (int j0 = 0; j0 < NH; j0 += NB) {
             float hc[NB], hv[NB];
             uint8_t hm[NB];
@@ -103,7 +104,7 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
             Pt[2 * t + 1] = (F * F) * (p * p);
         }
         __syncthreads();
-#pragma unroll 1
+#pragma unroll (ROLLED ? 1 : K)
         for (int dv = 0; dv < K; ++dv) {
             // the windows of this PSF row as 16-byte reads (rows are 16-byte
             // aligned; the last read may pass the window by up to three
@@ -140,7 +141,7 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
 }
 
 template <int R>
-__global__ __launch_bounds__(NTHR) void matched_kernel(MatchedArgs a) {
+__global__ __launch_bounds__(NTHR, R == 3 ? 3 : 2) void matched_kernel(MatchedArgs a) {
     extern __shared__ __align__(16) float lds[];
     const int tid = threadIdx.x;
     const int bx0 = (blockIdx.x % a.bx) * BW, by0 = (blockIdx.x / a.bx) * BH;
@@ -541,16 +542,27 @@ int launch_coadd_matched(argus_ctx *ctx, argus_dims d, int n, const float *const
     a.pitch = d.pitch; a.W = d.width; a.H = d.height; a.n = n;
     a.bx = (d.width + BW - 1) / BW;
     const int nblocks = a.bx * ((d.height + BH - 1) / BH);
+    // The matrix form (up to r = 8: an operand of 32 rows holds 16 + 2 r taps) pays
+    // for its splits from r = 5 on, or where there are backgrounds, whose
+    // interpolation its staging shares among columns, from r = 3 on and at r = 1
+    // (3 PSF rows are one turn of its 4 waves, 5 are two).  4788x3194, 5 images,
+    // FP32 / matrix form (us): no backgrounds r = 1 339 / 483, 2 411 / 648, 3 532 /
+    // 648, 4 663 / 757, 5 980 / 847; with them r = 1 565 / 536, 2 654 / 709, 3 788 /
+    // 696, 4 951 / 811.  500x333, 2 images: 4 29 / 27, 5 36 / 28; 3 with them 35 / 28.
+    bool grid = false;
+    for (int j = 0; j < n; ++j) grid = grid || a.bg[j].grid;
+    const bool fp32 = grid ? r == 2 : r <= 4;
     argus_time_begin(ctx);
     int rc;
     switch (r) {
-        // (a Toeplitz operand of 32 rows holds 16 + 2 r taps up to r = 8)
-#define ARGUS_MR(RR) case RR: rc = matched_mfma_launch<RR>(ctx, a); break;
-        ARGUS_MR(1) ARGUS_MR(2) ARGUS_MR(3) ARGUS_MR(4) ARGUS_MR(5) ARGUS_MR(6) ARGUS_MR(7)
-        ARGUS_MR(8)
-#undef ARGUS_MR
-        case 9: rc = matched_launch<9>(ctx, a, nblocks); break;
-        case 10: rc = matched_launch<10>(ctx, a, nblocks); break;
+#define ARGUS_MF(RR) case RR: rc = matched_launch<RR>(ctx, a, nblocks); break;
+#define ARGUS_MM(RR) case RR: rc = matched_mfma_launch<RR>(ctx, a); break;
+#define ARGUS_ME(RR) case RR: rc = fp32 ? matched_launch<RR>(ctx, a, nblocks) : matched_mfma_launch<RR>(ctx, a); break;
+        ARGUS_ME(1) ARGUS_ME(2) ARGUS_ME(3) ARGUS_ME(4) ARGUS_MM(5) ARGUS_MM(6) ARGUS_MM(7) ARGUS_MM(8)
+        ARGUS_MF(9) ARGUS_MF(10)
+#undef ARGUS_MF
+#undef ARGUS_MM
+#undef ARGUS_ME
         default: return argus_fail(ctx, ARGUS_ESHAPE, "psf_half %d not in 1..10", r);
     }
     if (rc) return rc;

@@ -151,3 +151,26 @@ def test_zero_points_and_units(ctx, u, F):
     pos = oV > 0
     assert np.abs(V[pos].astype(np.float64) / float(np.float32(F)) ** 2 * u * u / oV[pos] - 1).max() <= 1e-5
     assert (np.abs(N - oN) - 1e-6 * np.abs(oN)).max() <= 1e-4
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("grid", [False, True])
+def test_either_form_of_a_half_width(ctx, r, grid):
+    """Small half-widths, which take the FP32 or the matrix form by whether the
+    images have backgrounds: constant grids against the frames less the constant."""
+    import torch
+    W, H, n = 141, 67, 2
+    fr = _frames(W, H, n, 50 + r)
+    psfs = np.stack([synth.psf_image(r, 1.5)] * n).astype(np.float32)
+    sky = 64.0
+    d = [[dev(c + np.float32(sky)) if grid else dev(c), dev(v), dev(m)] for c, v, m in fr]
+    out = [empty((H, W), torch.float32) for _ in range(3)]
+    grids = [torch.full((-(-H // 32), -(-W // 32)), sky, device="cuda") for _ in range(n)] if grid else None
+    ctx.coadd_matched([f[0] for f in d], [f[1] for f in d], [f[2] for f in d], dev(psfs), r, *out,
+                      grids=grids, box=32)
+    cal = [host(f[0]).astype(np.float64) - (sky if grid else 0.0) for f in d]
+    S, V, N = matched.matched_coadd(cal, [f[1] for f in fr], [f[2] for f in fr], [None] * n,
+                                    [p.astype(np.float64) for p in psfs], [1.0] * n)
+    pos = V > 0
+    assert np.abs(host(out[1])[pos] / V[pos] - 1).max() <= 1e-5
+    assert (np.abs(host(out[2]) - N) - 1e-6 * np.abs(N)).max() <= 1e-4
