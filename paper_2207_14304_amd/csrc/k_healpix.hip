@@ -19,7 +19,8 @@
 // so the block's bounding box of the frame (46 x 46 at equal scales, twice the
 // block's area) is staged in LDS with row loads and the neighbours are read
 // there.  210 segments of 600^2 pixels of the full frame: 1178 -> 519 us (of
-// which the gathers took 700 us from global memory).
+// which the gathers took 700 us from global memory).  Coarser segments, whose
+// boxes do not fit, gather from the frame, a pixel a thread.
 #include <algorithm>
 #include <set>
 #include <tuple>
@@ -42,8 +43,6 @@ struct HpArgs {
     int W, H, nside, m;
 };
 
-constexpr int BOX = 2250;              // frame pixels that the LDS box holds
-
 // 1 / v for a normal v: the hardware estimate and two Newton steps
 __device__ __forceinline__ double recip(double v) {
     double r = __builtin_amdgcn_rcp(v);
@@ -51,11 +50,12 @@ __device__ __forceinline__ double recip(double v) {
     return fma(fma(-v, r, 1.0), r, r);
 }
 
-// BS x BS pixels a workgroup.  BOXED: neighbours from the box in LDS, a wave on
-// rows of the block (whole-line stores); else from the frame, a wave on 8 x 8
-// patches (whose neighbours lie on the fewest lines).
-template <int BS, bool BOXED>
-__global__ __launch_bounds__(256, 7) void healpix_resample_kernel(HpArgs a) {
+// BS x BS pixels a workgroup.  BOX > 0: neighbours from a box of at most BOX
+// frame pixels in LDS, a wave on rows of the block (whole-line stores); else from
+// the frame, a wave on 8 x 8 patches (whose neighbours lie on the fewest lines).
+template <int BS, int BOX, int WG>
+__global__ __launch_bounds__(256, WG) void healpix_resample_kernel(HpArgs a) {
+    constexpr bool BOXED = BOX > 0;
     constexpr int ND = 2 * BS - 1;             // diagonals of a block
     constexpr int NK = BS * BS / 256;          // pixels of a thread
     constexpr int CAP = BOXED ? BOX : 1;
@@ -241,24 +241,25 @@ int launch_resample_healpix(argus_ctx *ctx, argus_dims d, const float *cal, cons
     a.cal = cal; a.var = var; a.mask = mask; a.tiles = tiles;
     a.out = out; a.outv = out_var; a.outm = out_mask;
     a.pitch = d.pitch; a.W = d.width; a.H = d.height; a.nside = nside; a.m = m;
-    // side of a segment pixel in frame pixels, and the block whose box fits (a
-    // square turned by 45 degrees): 32 x 32 up to equal scales (full frame, 600^2
-    // pixels: 519 us; 16 x 16 takes 980), 16 x 16 up to twice the frame's
-    // (300^2: 322 us; no box 438, one pixel a thread in rows 505), else no box
+    // Side of a segment pixel in frame pixels, and the smallest box that 32 x 32
+    // segment pixels turned by 45 degrees fit (larger boxes leave fewer workgroups
+    // on a CU); past the largest (64 columns, a wave's row) single gathers.  207
+    // segments of the full frame (us): 600^2 (scale 1) box of 2250 574, 3000 635,
+    // none 868; 550^2 (1.09) 3000 628, 4000 678, none 791; 450^2 (1.33) 4000 480,
+    // none 577; without a box 300^2 328, 150^2 187, 60^2 91, where blocks of 32 x 32
+    // take 436, 248, 110 and boxes of 16 x 16 342, 249, 100.
     const double seg = sqrt(4.0 * PI / 12.0) / ((double)nside * m) * (180.0 / PI);
     const double ratio = seg / sqrt(fabs(a.w.cd[0] * a.w.cd[3] - a.w.cd[1] * a.w.cd[2]));
-    auto fits = [&](int bs) {
-        const double side = bs * ratio * 1.41421356 + 2.0;
-        return side * side <= (double)BOX;
-    };
+    const double side = 32 * ratio * 1.41421356 + 2.0, area = side * side;
     argus_time_begin(ctx);
     auto launch = [&](auto kernel, int bs) {
         const int nx = (m + bs - 1) / bs;
         hipLaunchKernelGGL(kernel, dim3(nx * nx, n_tiles), dim3(256), 0, ctx->stream, a);
     };
-    if (fits(32)) launch(healpix_resample_kernel<32, true>, 32);
-    else if (fits(16)) launch(healpix_resample_kernel<16, true>, 16);
-    else launch(healpix_resample_kernel<32, false>, 32);
+    if (area <= 2250.0) launch(healpix_resample_kernel<32, 2250, 7>, 32);
+    else if (area <= 3000.0) launch(healpix_resample_kernel<32, 3000, 5>, 32);
+    else if (area <= 4000.0) launch(healpix_resample_kernel<32, 4000, 4>, 32);
+    else launch(healpix_resample_kernel<16, 0, 7>, 16);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     argus_time_end(ctx, "healpix_resample");
     return ARGUS_OK;

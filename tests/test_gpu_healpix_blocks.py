@@ -60,3 +60,10 @@ def test_blocks(W, H, ra0, dec0, rot, scale, nside, m):
         assert _ulps(g[ok], val[ok]).max() <= 2 and _ulps(gv[ok], vv[ok]).max() <= 2
     assert np.all(g[gm != 0] == 0) and np.all(gv[gm != 0] == 0)
     ctx.close()
+
+
+@pytest.mark.parametrize("rot,m", [(0.785, 560), (0.1, 530), (0.785, 450), (0.3, 447)])
+def test_larger_boxes(rot, m):
+    """Segments a little coarser than the frame: boxes of 3000 and 4000 pixels,
+    with the frame along the segment's diagonals (widest box) and across them."""
+    test_blocks(700, 600, 83.6, 33.0, rot, 1.38, 256, m)
