@@ -442,8 +442,18 @@ int launch_subtract(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec,
     // 122, 1100x977 370 / 348, 4500x3000 2981 / 2876, 6000x4000 (11750 blocks)
     // 4709 / 4645, 9568x6380 (29925) 9157 / 9244.  Degree 0, which has half the
     // work to share: 600x500 (160 blocks) 111 / 108, 2000x1500 379 / 384.
+    // Narrow kernels have few taps to hide the loads of four pixels' windows behind,
+    // and turn earlier (the kernel alone, us): degree 0, h = 4, 700x500 (192 blocks)
+    // 17.7 / 21.9, 256x224 15.3 / 12.6; degree 1, h = 3, 1500x1000 (756) 31 / 27,
+    // 3000x2000 (3000) 72 / 77; degree 2, h = 2, 700x500 17.0 / 14.5, 1000x800 (400)
+    // 19.2 / 20.7; h = 5, 1500x1000 45 / 46, 3000x2000 139 / 153.
     const int64_t blocks8 = (int64_t)a.RX * a.RY * columns(8) * a.bpy;
-    const int pxt = blocks8 < (a.D > 0 ? 16384 : 256) ? 4 : 8;
+    const int h = spec->half_width;
+    int64_t limit = a.D > 0 ? 16384 : 256;
+    if (a.D == 0 && (h == 3 || h == 4)) limit = 128;
+    if (a.D == 1 && h >= 3 && h <= 6) limit = 1024;
+    if (a.D == 2 && h >= 2 && h <= 5) limit = h == 2 ? 256 : 1024;
+    const int pxt = blocks8 < limit ? 4 : 8;
     a.bpx = columns(pxt);
     a.sx = d.width > 1 ? 2.0 / (d.width - 1) : 0.0;
     a.sy = d.height > 1 ? 2.0 / (d.height - 1) : 0.0;

@@ -83,3 +83,15 @@ def test_unaligned_outputs_and_noalloc(ctx, off):
         res.append([host(x).copy() for x in (D, V, M, c2)])
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("D,h,W,H", [(0, 3, 1021, 256), (0, 4, 1024, 240), (2, 2, 1024, 512), (2, 2, 1024, 500),
+                                     (1, 3, 2048, 1024), (2, 5, 2045, 1000)])
+def test_narrow_kernels_turn_earlier(ctx, D, h, W, H):
+    """On and one row of blocks under the block counts where narrow kernels go
+    from four to eight pixels a thread."""
+    spec = _spec(half_width=h, spatial_degree=D, bg_degree=min(D, 1))
+    st, bg = _stamps(spec, 1, W)
+    planes = _planes(W, H, W + H)
+    g = _run_subtract(ctx, spec, st, bg, planes)
+    _check_subtract(g, oracle.subtract(st, bg, *planes, _ospec(spec)))
