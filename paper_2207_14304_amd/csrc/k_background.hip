@@ -32,7 +32,7 @@ struct CellArgs {
     float *levels;
     int64_t pitch;
     int W, H, box, gx, gy;
-    int vec;                           // 16-byte rows of cal, 4-byte rows of mask
+    int vec;                           // 16-byte rows of cal, 4-byte rows of mask, cells on them
 };
 
 // What bounds this kernel is instruction issue and LDS atomics, not its 5
@@ -265,7 +265,8 @@ int launch_background(argus_ctx *ctx, argus_dims d, const float *cal, const uint
         if (rc) return rc;
         lev = (float *)ctx->ws;
     }
-    const int vec = d.pitch % 4 == 0 && (uintptr_t)cal % 16 == 0 && (uintptr_t)mask % 4 == 0;
+    // (cells of 33..63 columns may end in one of 32 that starts between words)
+    const int vec = d.pitch % 4 == 0 && (uintptr_t)cal % 16 == 0 && (uintptr_t)mask % 4 == 0 && box % 4 == 0;
     CellArgs a{cal, mask, lev, d.pitch, d.width, d.height, box, gx, gy, vec};
     argus_time_begin(ctx);
     hipLaunchKernelGGL(bg_cell_kernel, dim3(gx * gy), dim3(NTHR), 0, ctx->stream, a);
