@@ -99,7 +99,7 @@ struct BatchArgs {
     const BasisTables *tab;
     double *part, *c2;
     float *stamps;
-    int ntask, nb, n_unk, shape;
+    int ntask, nb, n_unk, shape, tile0;    // tile0: first tile of a launch
     int8_t plist[4][4];
     float thr;
     float *diff, *dvar;
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(256, 4) void batch_subtract_kernel(BatchArgs a) {
     __shared__ uint64_t M[TH];                       // footprint along the row, per input row
     __shared__ double red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bid = argus_xcd_block(blockIdx.x, gridDim.x);
+    const int bid = a.tile0 + argus_xcd_block(blockIdx.x, gridDim.x);
     const int c = a.tile[bid];
     const BCut cu = a.cuts[c];
     const argus_frame fr = a.frames[cu.frame];
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(256) void batch_detect_kernel(BatchArgs a, const in
     __shared__ float s[TH][SWD + 2];
     __shared__ int cnt[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bid = argus_xcd_block(blockIdx.x, gridDim.x);
+    const int bid = a.tile0 + argus_xcd_block(blockIdx.x, gridDim.x);
     const int c = tiles[bid];
     const BCut cu = a.cuts[c];
     const int L = cu.side, j = bid - cu.tile0[1], ntx = (L + BW - 1) / BW;
@@ -919,12 +919,21 @@ int batch_launch_t(argus_ctx *ctx, const argus_batch *b, BatchArgs ba, int tile,
     }
     ba.shape = tile == 16 ? 0 : 1;
     ba.tile = b->d_tile[ba.shape];
-    const dim3 tiles(b->ntile[ba.shape]);
-    if (tile == 16)
-        hipLaunchKernelGGL((batch_subtract_kernel<HH, 16>), tiles, dim3(256), 0, st, ba);
-    else
-        hipLaunchKernelGGL((batch_subtract_kernel<HH, 32>), tiles, dim3(256), 0, st, ba);
-    hipLaunchKernelGGL(batch_detect_kernel, dim3(b->ntile[1]), dim3(256), 0, st, ba, b->d_tile[1]);
+    // (a launch holds less than 2^32 threads)
+    constexpr int MOST = 1 << 23;
+    for (int64_t t = 0; t < b->ntile[ba.shape]; t += MOST) {
+        ba.tile0 = (int)t;
+        const dim3 tiles((unsigned)std::min<int64_t>(MOST, b->ntile[ba.shape] - t));
+        if (tile == 16)
+            hipLaunchKernelGGL((batch_subtract_kernel<HH, 16>), tiles, dim3(256), 0, st, ba);
+        else
+            hipLaunchKernelGGL((batch_subtract_kernel<HH, 32>), tiles, dim3(256), 0, st, ba);
+    }
+    for (int64_t t = 0; t < b->ntile[1]; t += MOST) {
+        ba.tile0 = (int)t;
+        const dim3 tiles((unsigned)std::min<int64_t>(MOST, b->ntile[1] - t));
+        hipLaunchKernelGGL(batch_detect_kernel, tiles, dim3(256), 0, st, ba, b->d_tile[1]);
+    }
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
     return ARGUS_OK;
 }
