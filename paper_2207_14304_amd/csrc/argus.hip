@@ -39,6 +39,7 @@ int argus_ws_reserve(argus_ctx *ctx, size_t bytes) {
     }
     size_t want = bytes + (bytes >> 3);
     if (hipMalloc(&ctx->ws, want) != hipSuccess) {
+        (void)hipGetLastError();               // (else the next launch's check would report it)
         ctx->ws = nullptr;
         return argus_fail(ctx, ARGUS_ENOMEM, "workspace allocation of %zu bytes failed", want);
     }

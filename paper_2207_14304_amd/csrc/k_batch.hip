@@ -26,6 +26,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "fit_accum.h"
@@ -956,14 +958,12 @@ inline int ilog2(int64_t v) {
 
 }  // namespace
 
-extern "C" {
+namespace {
 
-int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_cutout *cutouts,
-                     int n_cutouts, const int32_t *frame_widths, const int32_t *frame_heights,
-                     int n_frames, argus_batch **out) {
-    if (!ctx || !out) return ARGUS_EINVAL;
-    ctx->err.clear();
-    *out = nullptr;
+// (throws std::bad_alloc when host memory runs out)
+int batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_cutout *cutouts,
+               int n_cutouts, const int32_t *frame_widths, const int32_t *frame_heights,
+               int n_frames, argus_batch **out) {
     int nu, ns;
     int rc = argus_kernel_dims(spec, &nu, &ns);
     if (rc) return argus_fail(ctx, rc, "argus_batch_plan: bad kernel spec");
@@ -986,7 +986,8 @@ int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_
             return argus_fail(ctx, ARGUS_ESHAPE, "cutout %d leaves its frame", i);
         if (c.out_offset < 0) return argus_fail(ctx, ARGUS_EINVAL, "cutout %d: negative offset", i);
     }
-    argus_batch *b = new argus_batch();
+    std::unique_ptr<argus_batch, void (*)(argus_batch *)> hold(new argus_batch(), argus_batch_destroy);
+    argus_batch *b = hold.get();
     for (int i = 0; i < n_cutouts; ++i) b->area += (int64_t)cutouts[i].side * cutouts[i].side;
     b->n = n_cutouts;
     b->n_frames = n_frames;
@@ -1050,10 +1051,8 @@ int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_
         for (int s = 0; s < 2; ++s) {
             const int th = s ? 32 : 16;
             const size_t k = (size_t)((q.side + BW - 1) / BW) * ((q.side + th - 1) / th);
-            if (tile[s].size() + k > (size_t)INT32_MAX) {
-                delete b;
+            if (tile[s].size() + k > (size_t)INT32_MAX)
                 return argus_fail(ctx, ARGUS_ESHAPE, "batch of more than 2^31 tiles");
-            }
             cu.tile0[s] = (int32_t)tile[s].size();
             tile[s].insert(tile[s].end(), k, c);
         }
@@ -1075,7 +1074,7 @@ int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_
                  off_p = place((size_t)part_max * PST * 8), off_s = place(tile[0].size() * 8),
                  off_st = place((size_t)n_cutouts * stamp_stride(h) * 4);
     if (hipMalloc(&b->dev, bytes) != hipSuccess) {
-        delete b;
+        (void)hipGetLastError();               // (else the next launch's check would report it)
         return argus_fail(ctx, ARGUS_ENOMEM, "batch tables");
     }
     char *dev = (char *)b->dev;
@@ -1097,21 +1096,31 @@ int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_
         hipMemcpy(b->d_tile[1], tile[1].data(), tile[1].size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming) != hipSuccess) {
-        argus_batch_destroy(b);
+        hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming) != hipSuccess)
         return argus_fail(ctx, ARGUS_EHIP, "batch setup failed");
-    }
-    if ((rc = launch_basis_tables_to(ctx, spec, b->d_tables))) {
-        argus_batch_destroy(b);
-        return rc;
-    }
+    if ((rc = launch_basis_tables_to(ctx, spec, b->d_tables))) return rc;
     // the basis tables must be complete before the private stream reads them
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
-        argus_batch_destroy(b);
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess)
         return argus_fail(ctx, ARGUS_EHIP, "batch setup sync failed");
-    }
-    *out = b;
+    *out = hold.release();
     return ARGUS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int argus_batch_plan(argus_ctx *ctx, const argus_kernel_spec *spec, const argus_cutout *cutouts,
+                     int n_cutouts, const int32_t *frame_widths, const int32_t *frame_heights,
+                     int n_frames, argus_batch **out) {
+    if (!ctx || !out) return ARGUS_EINVAL;
+    ctx->err.clear();
+    *out = nullptr;
+    try {
+        return batch_plan(ctx, spec, cutouts, n_cutouts, frame_widths, frame_heights, n_frames, out);
+    } catch (const std::bad_alloc &) {
+        return argus_fail(ctx, ARGUS_ENOMEM, "batch tables of %d cutouts: out of host memory", n_cutouts);
+    }
 }
 
 int argus_batch_run(argus_ctx *ctx, argus_batch *b, const argus_frame *frames, float threshold,
