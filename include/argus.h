@@ -132,9 +132,9 @@ int  argus_ctx_set_stream(argus_ctx *ctx, void *hip_stream);
 /* Tuning cache of the autotuner (argus_batch_run's tile-shape search): each
  * search's outcome -- the chosen candidate and every candidate's time -- is
  * kept on the context under a key naming the device (architecture name and
- * compute-unit count), the HIP runtime version, the kernel, its half width,
- * precision and problem-size bucket (log2 of the cutout count and of the
- * summed cutout area); a later search with the same key takes the stored
+ * compute-unit count), the HIP runtime version, the kernel and its form, its
+ * half width, precision and problem-size bucket (log2 of the cutout count and
+ * of the summed cutout area); a later search with the same key takes the stored
  * choice without timing.  With a path (or, at context creation, the file
  * named by the ARGUS_TUNE_CACHE environment variable) the entries are read
  * from that file now and every new one is appended to it, one JSON object

@@ -1161,10 +1161,11 @@ int argus_batch_run(argus_ctx *ctx, argus_batch *b, const argus_frame *frames, f
         ba.coeffs = coeffs; ba.chi2 = chi2; ba.n_fit = n_fit; ba.status = status; ba.n_cands = n_cands;
         if (b->choice < 0) {
             // autotune: the context's cache (device, HIP runtime, kernel, half
-            // width, precision, size bucket), else time each candidate once on
+            // width, precision, size bucket, and the form of the kernels: times of
+            // another form say nothing here), else time each candidate once on
             // these inputs and store the outcome
             char kb[160];
-            snprintf(kb, sizeof kb, ";kernel=batch;h=%d;prec=%d;log2n=%d;log2area=%d", b->h,
+            snprintf(kb, sizeof kb, ";kernel=batch;h=%d;prec=%d;log2n=%d;log2area=%d;form=tasks", b->h,
                      b->spec.precision, ilog2(b->n), ilog2(b->area));
             const std::string key = argus_tune_device_key(ctx) + kb;
             const argus_ctx::Tuned *t = argus_tune_lookup(ctx, key);

@@ -112,3 +112,27 @@ def test_several_rounds(ctx, frame):
     for k in ("coeffs", "chi2", "n_fit", "status", "n_cands"):
         v = o[k]
         assert bool((v == v[:1]).all()), k
+
+
+def test_times_of_another_form_are_not_taken(frame, tmp_path):
+    """A tuning file written for the one-workgroup-per-cutout kernel (its keys
+    name no form) does not choose for these kernels."""
+    import json
+
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    path, old = tmp_path / "tune.jsonl", tmp_path / "old.jsonl"
+    for p, from_file in ((path, False), (path, True), (old, False)):
+        c = argus.Context(0)
+        c.set_tune_cache(p)
+        b, _ = _run(c, frame, [3, 20], [4, 9], [80, 130], 7)
+        ms, hit = b.tuning()
+        assert hit == from_file and max(ms) < 1e4
+        b.close()
+        c.close()
+        if p is path:
+            entry = json.loads(path.read_text().splitlines()[0])
+            key = entry["key"].rsplit(";form=", 1)
+            assert len(key) == 2
+            old.write_text(json.dumps(dict(entry, key=key[0], ms=[1e6] * len(entry["ms"]))) + "\n")
