@@ -136,3 +136,22 @@ def test_times_of_another_form_are_not_taken(frame, tmp_path):
             key = entry["key"].rsplit(";form=", 1)
             assert len(key) == 2
             old.write_text(json.dumps(dict(entry, key=key[0], ms=[1e6] * len(entry["ms"]))) + "\n")
+
+
+@pytest.mark.parametrize("h,sides", [(4, [73, 137]), (7, [77, 143, 271]), (10, [85, 149, 512])])
+def test_fp64_differences(ctx, frame, h, sides):
+    """FP64 moments hold the bar of the frame's differences, RMS 1e-4 sigma."""
+    H, W = frame[0].shape
+    side = np.array(sides)
+    x0, y0 = np.minimum(13 * np.arange(len(side)) + 2, W - side), np.minimum(5, H - side)
+    b, o = _run(ctx, frame, x0, y0, side, h)
+    spec = oracle.KernelSpec(half_width=h)
+    for i, L in enumerate(sides):
+        planes = [p[y0[i]:y0[i] + L, x0[i]:x0[i] + L] for p in frame]
+        co, _, _ = oracle.fit_kernel(*planes, spec)
+        D, V, dm, _, _ = oracle.subtract(*oracle.expand_kernel(co, spec), *planes, spec)
+        d = host(o["diff"])[b.offsets[i]:b.offsets[i] + L * L].reshape(L, L)
+        ok = dm == 0
+        rms = np.sqrt(np.mean((d[ok] - D[ok]) ** 2 / V[ok]))
+        print(f"h {h} side {L}: RMS {rms:.1e}")
+        assert rms <= 1e-4
