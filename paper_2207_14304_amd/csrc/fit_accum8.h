@@ -539,61 +539,60 @@ __device__ void fit_mfma8(const FitArgs &a, float *lds, int sx_begin, int sx_end
                         yprev = y;
                     }
                 }
-                __syncthreads();
-                continue;
-            }
-            // moments of output row y = yy - 1 - h, written during the previous step
-            const int y = yy - 1 - HH;
-            if (yy - 1 >= ry0 + HH && yy - 1 < yend) {
-                const int pb = buf ^ 1;
-                double ypw[2 * D + 1];
-                if constexpr (DEFER) {
-                    if (have) {
-                        ypowers(yprev, ypw);
-                        gram.flush(acc, ypw);
+            } else {
+                // moments of output row y = yy - 1 - h, written during the previous step
+                const int y = yy - 1 - HH;
+                if (yy - 1 >= ry0 + HH && yy - 1 < yend) {
+                    const int pb = buf ^ 1;
+                    double ypw[2 * D + 1];
+                    if constexpr (DEFER) {
+                        if (have) {
+                            ypowers(yprev, ypw);
+                            gram.flush(acc, ypw);
+                        }
                     }
-                }
-                ypowers(y, ypw);
-                if constexpr (!DEFER) gram.row_km(l.cvec(pb), l.wx(pb), l.wxd(pb), ypw, lane, g0, g1);
-                const float *cv = l.cvec(pb);
-                const int k = lane & 31, half = lane >> 5;
-                if constexpr (PREC == ARGUS_FP64) {
-                    double ra[S::NRA];
+                    ypowers(y, ypw);
+                    if constexpr (!DEFER) gram.row_km(l.cvec(pb), l.wx(pb), l.wxd(pb), ypw, lane, g0, g1);
+                    const float *cv = l.cvec(pb);
+                    const int k = lane & 31, half = lane >> 5;
+                    if constexpr (PREC == ARGUS_FP64) {
+                        double ra[S::NRA];
 #pragma unroll
-                    for (int e = 0; e < S::NRA; ++e) ra[e] = 0.0;
+                        for (int e = 0; e < S::NRA; ++e) ra[e] = 0.0;
 #pragma unroll
-                    for (int i = 0; i < PXH; ++i) {
-                        const int px = MW * PXW + half * PXH + i;
-                        const double c = (double)cv[k * L::CKM + px] + (double)gk * (double)cv[px];
+                        for (int i = 0; i < PXH; ++i) {
+                            const int px = MW * PXW + half * PXH + i;
+                            const double c = (double)cv[k * L::CKM + px] + (double)gk * (double)cv[px];
 #pragma unroll
-                        for (int e = 0; e < S::NRA; ++e) ra[e] += l.wsxd(pb)[e * SW + px] * c;
+                            for (int e = 0; e < S::NRA; ++e) ra[e] += l.wsxd(pb)[e * SW + px] * c;
+                        }
+#pragma unroll
+                        for (int e = 0; e < S::NRA; ++e)
+#pragma unroll
+                            for (int b = 0; b <= D; ++b)
+                                if (e + b <= D) RF[qidx(e, b, D)] += ypw[b] * ra[e];
+                    } else {
+                        float ra[S::NRA];
+#pragma unroll
+                        for (int e = 0; e < S::NRA; ++e) ra[e] = 0.f;
+#pragma unroll
+                        for (int i = 0; i < PXH; ++i) {
+                            const int px = MW * PXW + half * PXH + i;
+                            const float c = cv[k * L::CKM + px] + gk * cv[px];
+#pragma unroll
+                            for (int e = 0; e < S::NRA; ++e) ra[e] += l.wsx(pb)[e * SW + px] * c;
+                        }
+#pragma unroll
+                        for (int e = 0; e < S::NRA; ++e)
+#pragma unroll
+                            for (int b = 0; b <= D; ++b)
+                                if (e + b <= D) RF[qidx(e, b, D)] += ypw[b] * (double)ra[e];
                     }
-#pragma unroll
-                    for (int e = 0; e < S::NRA; ++e)
-#pragma unroll
-                        for (int b = 0; b <= D; ++b)
-                            if (e + b <= D) RF[qidx(e, b, D)] += ypw[b] * ra[e];
-                } else {
-                    float ra[S::NRA];
-#pragma unroll
-                    for (int e = 0; e < S::NRA; ++e) ra[e] = 0.f;
-#pragma unroll
-                    for (int i = 0; i < PXH; ++i) {
-                        const int px = MW * PXW + half * PXH + i;
-                        const float c = cv[k * L::CKM + px] + gk * cv[px];
-#pragma unroll
-                        for (int e = 0; e < S::NRA; ++e) ra[e] += l.wsx(pb)[e * SW + px] * c;
+                    if constexpr (DEFER) {
+                        gram.row_km_acc(l.cvec(pb), l.wx(pb), l.wxd(pb), lane, g0, g1, acc);
+                        have = true;
+                        yprev = y;
                     }
-#pragma unroll
-                    for (int e = 0; e < S::NRA; ++e)
-#pragma unroll
-                        for (int b = 0; b <= D; ++b)
-                            if (e + b <= D) RF[qidx(e, b, D)] += ypw[b] * (double)ra[e];
-                }
-                if constexpr (DEFER) {
-                    gram.row_km_acc(l.cvec(pb), l.wx(pb), l.wxd(pb), lane, g0, g1, acc);
-                    have = true;
-                    yprev = y;
                 }
             }
             __syncthreads();

@@ -28,23 +28,6 @@ __host__ __device__ inline void face_centre(int f, double &xc, double &yc) {
     else { xc = QP + (f - 8) * HP; yc = -QP; }
 }
 
-// plane point -> (z, phi), phi in [0, 2 pi)
-__host__ __device__ inline void plane_to_sphere(double xs, double ys, double &z, double &phi) {
-    xs = fmod(xs, TWO_PI);
-    if (xs < 0) xs += TWO_PI;
-    if (fabs(ys) <= QP) {
-        z = ys * (8.0 / (3.0 * PI));
-        phi = xs;
-        return;
-    }
-    const double sig = 2.0 - fabs(ys) / QP;
-    z = (ys > 0 ? 1.0 : -1.0) * (1.0 - sig * sig / 3.0);
-    const double phic = QP + floor(xs / HP) * HP;
-    phi = sig > 0 ? phic + (xs - phic) / sig : phic;
-    phi = fmod(phi, TWO_PI);
-    if (phi < 0) phi += TWO_PI;
-}
-
 // (z, phi) -> plane point
 __host__ __device__ inline void sphere_to_plane(double z, double phi, double &xs, double &ys) {
     phi = fmod(phi, TWO_PI);
@@ -103,22 +86,6 @@ inline bool make_wcs(const argus_wcs &w, Wcs &o) {
     o.cdi[2] = -w.cd[2] / det;
     o.cdi[3] = w.cd[0] / det;
     return true;
-}
-
-// direction (z = sin dec, ra radians) -> frame pixel; returns the projection
-// denominator (<= 0: the far side of the tangent plane)
-__host__ __device__ inline double sky_to_pixel(const Wcs &w, double z, double ra, double &x,
-                                               double &y) {
-    const double cdd = sqrt(fmax(1.0 - z * z, 0.0));
-    double s, c;
-    sincos(ra - w.ra0, &s, &c);
-    const double den = z * w.sd0 + cdd * w.cd0 * c;
-    const double r2d = 180.0 / PI;
-    const double xi = r2d * cdd * s / den;
-    const double eta = r2d * (z * w.cd0 - cdd * w.sd0 * c) / den;
-    x = w.cdi[0] * xi + w.cdi[1] * eta + w.crpix1;
-    y = w.cdi[2] * xi + w.cdi[3] * eta + w.crpix2;
-    return den;
 }
 
 // frame pixel -> direction (z = sin dec, ra radians in [0, 2 pi))

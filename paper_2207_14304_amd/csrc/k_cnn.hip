@@ -256,7 +256,7 @@ __global__ __launch_bounds__(CT, CPW) void cnn_conv32_kernel(ConvArgs a) {
             __threadfence_block();
             __syncthreads();
             const bf16 *dst = a.out + (size_t)s * a.npx * 32;
-            const int p0 = y0 * W, p1 = min(a.npx, p0 + BAND * W), ntile = (p1 - p0 + 15) / 16;
+            const int p0 = y0 * W, p1 = min(a.npx, p0 + BAND * W);
             float ps0 = 0.f, ps1 = 0.f;
             uint32_t w[8][4];
 #pragma unroll
