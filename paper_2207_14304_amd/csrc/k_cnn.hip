@@ -1420,7 +1420,7 @@ int conv_launch(argus_ctx *ctx, const ConvArgs &ca) {
     static_assert(CIN == 32 || (CIN == 2 && MODE == 0), "first layer forward, the others both ways");
     const dim3 grid(ca.n * NBAND);
     if constexpr (CIN == 32)
-        hipLaunchKernelGGL(cnn_conv32_kernel<MODE>, dim3(std::min(ca.n * NBAND, ctx->n_cu * CPW)), dim3(CT), 0, ctx->stream, ca);
+        hipLaunchKernelGGL(cnn_conv32_kernel<MODE>, dim3(std::min(ca.n * NBAND, (ctx->n_cu > 0 ? ctx->n_cu : 256) * CPW)), dim3(CT), 0, ctx->stream, ca);
     else
         hipLaunchKernelGGL(cnn_conv2_kernel, grid, dim3(CT), 0, ctx->stream, ca);
     ARGUS_HIP_CHECK(ctx, hipGetLastError());
