@@ -200,6 +200,7 @@ struct RowArgs {
     cplx *Z;                           // [n][k_x][y]
     uint64_t *bits;                    // [n][y][L / 64]: flagged along x within rad
     double g;                          // scale of R
+    double *gp;                        // scale of the reference's PSF, written by the PSF pass
 };
 
 // OR of the bits of the word `c` and its neighbours within rad (< 64) places
@@ -215,8 +216,8 @@ __device__ __forceinline__ uint64_t dilate_bits(uint64_t p, uint64_t c, uint64_t
     return (uint64_t)(up >> 64) | (uint64_t)dn;
 }
 
-// Row transforms of N + i g R (PSF: of the stamps N and R, a plane each, wrapped
-// onto the tile, centre at the origin).
+// Row transforms of N + i g R (PSF: of the two stamps wrapped onto the tile,
+// centre at the origin, g from their maxima).
 template <int LG, bool PSF>
 __global__ __launch_bounds__(512) void zogy_rows_kernel(RowArgs a) {
     using F = Fft<LG>;
@@ -229,12 +230,34 @@ __global__ __launch_bounds__(512) void zogy_rows_kernel(RowArgs a) {
     cplx v[8];
     if constexpr (PSF) {
         const int dv = y <= L / 2 ? y : y - L, K = 2 * a.r + 1;
+        __shared__ float top[2][8];
+        float mn = 0.f, mr = 0.f;
+        for (int i = tid; i < K * K; i += 512) {
+            mn = fmaxf(mn, fabsf(a.N[i]));
+            mr = fmaxf(mr, fabsf(a.R[i]));
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            mn = fmaxf(mn, __shfl_xor(mn, o));
+            mr = fmaxf(mr, __shfl_xor(mr, o));
+        }
+        if ((tid & 63) == 0) {
+            top[0][tid >> 6] = mn;
+            top[1][tid >> 6] = mr;
+        }
+        __syncthreads();
+        for (int i = 0; i < 8; ++i) {
+            mn = fmaxf(mn, top[0][i]);
+            mr = fmaxf(mr, top[1][i]);
+        }
+        const bool fin = mn > 0.f && mr > 0.f && mn < __builtin_inff() && mr < __builtin_inff();
+        const double g = fin ? ldexp(1.0, ilogbf(mn) - ilogbf(mr)) : 1.0;
+        if (blockIdx.x == 0 && tid == 0) *a.gp = g;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int x = u + r * T, du = x <= L / 2 ? x : x - L;
             const bool in = dv >= -a.r && dv <= a.r && du >= -a.r && du <= a.r;
             const int i = (dv + a.r) * K + du + a.r;
-            v[r] = make_double2(in ? (double)(t == 0 ? a.N : a.R)[i] : 0.0, 0.0);
+            v[r] = in ? make_double2(a.N[i], g * a.R[i]) : make_double2(0.0, 0.0);
         }
     } else {
         const int X0 = a.org[2 * t], Y = a.org[2 * t + 1] + y;
@@ -333,27 +356,27 @@ __device__ __forceinline__ double score_scale(double pd2) {
     return pd2 > 0.0 && pd2 < __builtin_inf() ? ldexp(1.0, -(ilogb(pd2) >> 1)) : 1.0;
 }
 
-// Filter values from the PSF planes, and each workgroup's sum of |P_D^|^2.
+// Filter values from the PSF plane, and each workgroup's sum of |P_D^|^2.
 template <int LG>
 __global__ __launch_bounds__(256) void zogy_filter_kernel(const cplx *Z, const cplx *tw, ZCoef c,
-                                                          double g, Filter fl, double *part) {
+                                                          double g, const double *gp, Filter fl,
+                                                          double *part) {
     using F = Fft<LG>;
     extern __shared__ cplx sm[];
     __shared__ double red[4];
     const Column<LG> col(sm);
-    const cplx *z = Z + (size_t)col.kx * F::L + col.u;
-    cplx vn[8], vr[8];
+    const double ip = 1.0 / *gp;
+    cplx v[8], m[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        vn[r] = z[r * F::T];
-        vr[r] = z[(size_t)F::L * F::L + r * F::T];
-    }
-    fft<LG, false>(vn, col.u, tw, col.own);
-    fft<LG, false>(vr, col.u, tw, col.own);
+    for (int r = 0; r < 8; ++r) v[r] = Z[(size_t)col.kx * F::L + col.u + r * F::T];
+    fft<LG, false>(v, col.u, tw, col.own);
+    col.mirrored(v, m);
     double s = 0.0;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        const cplx Pn = vn[r], Pr = vr[r];
+        cplx Pn, Pr;
+        split(v[r], m[r], Pn, Pr);
+        Pr = make_double2(ip * Pr.x, ip * Pr.y);
         const double an = Pn.x * Pn.x + Pn.y * Pn.y, ar = Pr.x * Pr.x + Pr.y * Pr.y;
         const double den = sqrt(c.sn2 * c.Fr * c.Fr * ar + c.sr2 * c.Fn * c.Fn * an);
         const double ia = den > 0.0 ? c.Fr / den : 0.0, ib = den > 0.0 ? c.Fn / den / g : 0.0;
@@ -510,9 +533,9 @@ int zogy_run(argus_ctx *ctx, ZCall &z) {
     p.N = z.psf_n;
     p.R = z.psf_r;
     p.Z = z.psf;
-    hipLaunchKernelGGL((zogy_rows_kernel<LG, true>), dim3(2 * (L / F::NF)), dim3(512), row_lds, st, p);
+    hipLaunchKernelGGL((zogy_rows_kernel<LG, true>), dim3(L / F::NF), dim3(512), row_lds, st, p);
     hipLaunchKernelGGL(zogy_filter_kernel<LG>, dim3(pairs), dim3(256), col_lds, st,
-                       (const cplx *)z.psf, (const cplx *)z.tw, z.c, z.rows.g, z.fl, z.part);
+                       (const cplx *)z.psf, (const cplx *)z.tw, z.c, z.rows.g, (const double *)z.rows.gp, z.fl, z.part);
     hipLaunchKernelGGL(zogy_pd2_kernel, dim3(1), dim3(64), 0, st, (const double *)z.part, pairs,
                        1.0 / ((double)L * L), z.pd2);
     hipLaunchKernelGGL((zogy_rows_kernel<LG, false>), dim3(z.n * (L / F::NF)), dim3(512), row_lds, st,
@@ -532,10 +555,10 @@ int launch_zogy(argus_ctx *ctx, argus_dims d, const float *N, const uint8_t *mn,
                 const float *psf_r, int r, double Fn, double Fr, double sn, double sr, float *D,
                 float *snr, float *flux, uint8_t *mask, double *pd2_out) {
     const size_t LL = (size_t)L * L;
-    // workspace: a spectrum plane per tile, the PSF planes, the filter values,
+    // workspace: a spectrum plane per tile, the PSF plane, the filter values,
     // twiddles, the flag bits, partial sums and sum P_D^2
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t o_psf = al(n * LL * sizeof(cplx)), o_a = o_psf + al(2 * LL * sizeof(cplx)),
+    const size_t o_psf = al(n * LL * sizeof(cplx)), o_a = o_psf + al(LL * sizeof(cplx)),
                  o_b = o_a + al(LL * sizeof(cplx)), o_q = o_b + al(LL * sizeof(cplx)),
                  o_tw = o_q + al(LL * sizeof(double)), o_bits = o_tw + al(L * sizeof(cplx)),
                  o_part = o_bits + al(n * LL / 8), o_pd2 = o_part + al(L * sizeof(double)),
@@ -559,7 +582,8 @@ int launch_zogy(argus_ctx *ctx, argus_dims d, const float *N, const uint8_t *mn,
     // (an FP32 image times 2^+-800 is a normal FP64 number)
     const int k = ilogb(Fn) - ilogb(Fr);
     const double g = ldexp(1.0, k < -800 ? -800 : k > 800 ? 800 : k);
-    z.rows = RowArgs{N, R, mn, mr, origins, d.pitch, d.width, d.height, r, 2 * r, z.tw, z.Z, bits, g};
+    z.rows = RowArgs{N, R, mn, mr, origins, d.pitch, d.width, d.height, r, 2 * r, z.tw, z.Z, bits, g,
+                     (double *)(ws + o_pd2) + 1};
     z.out = OutArgs{z.Z, z.tw, bits, z.pd2, D, snr, flux, mask, z.c.FD, r, 2 * r};
     switch (L) {
         case 64: return zogy_run<6>(ctx, z);
