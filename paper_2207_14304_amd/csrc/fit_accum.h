@@ -10,7 +10,8 @@
 // adds yt^b times them into FP64 running sums.
 //
 // Precisions of the per-row products and sums:
-//   ARGUS_FP32   FP32 operands, v_mfma_f32_16x16x4f32 over 64 pixels;
+//   ARGUS_FP32   FP32 operands, v_mfma_f32_16x16x4f32 over 64 pixels (wide
+//                frames, D >= 1: six BF16 products of three-way splits);
 //   ARGUS_FP64   FP64 operands, v_mfma_f64_16x16x4f64 (FP64 products and sums);
 //   ARGUS_BF16X3 x = hi + lo with hi, lo bf16 (round to nearest even), and
 //                A B ~ Ahi Bhi + Ahi Blo + Alo Bhi on v_mfma_f32_16x16x32_bf16
@@ -220,8 +221,8 @@ int fit_accum_launch_fp32(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, d
 // faster one on both sides of it (degree 2, 15 x 15, FP32 form / wide form:
 // 1100x977 154 / 132 us, 3000x2000 751 / 639, 6143x4100 2.85 / 2.42 ms, 9576x6388
 // 7.04 / 5.94; degree 1: 134 / 110 us, 607 / 484, 2.27 / 1.69 ms, 5.58 / 4.13).  It
-// stands where the frames' own FP32 rounding (1e-5 and more of a pixel below it)
-// would let every narrower difference move.
+// keeps narrower frames' results to the bit; moving it changes them by the FP32
+// rounding of either form.
 int fit_accum_launch_wide(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);
 constexpr int FIT_WIDE_MIN = 6144;
 int fit_accum_launch_fp64(argus_ctx *ctx, const argus_fit::FitArgs &fa, int D, dim3 grid);

@@ -41,7 +41,7 @@ struct CellArgs {
 // their first digit, so there a wave adds its first lane's digit with one
 // atomic (64 lanes on one address take 64 turns); each thread clears the bins
 // it scans, so a digit takes three barriers.  Full frame, 64 x 64 cells: 267 ->
-// 110 us, against four 8-bit digits scanned by one wave.
+// 122 us, against four 8-bit digits scanned by one wave.
 __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
     constexpr int NB = 2048, PER = NB / NTHR;
     __shared__ __align__(16) int hist[NB];
@@ -232,7 +232,7 @@ __global__ void bg_filter_kernel(const float *levels, float *grid, int gx, int g
 
 // Four columns x MAP_ROWS rows a thread: a column's node and weight are formed
 // once, and its values on the two node rows once per crossing of a cell centre,
-// so a pixel costs one subtraction, one FMA and its 4 bytes (139 -> 60 us on
+// so a pixel costs one subtraction, one FMA and its 4 bytes (139 -> 48 us on
 // the full frame against a pixel a thread).
 constexpr int MAP_ROWS = 16;
 __global__ __launch_bounds__(NTHR) void bg_map_kernel(BgGrid g, float *map, int64_t pitch, int W,

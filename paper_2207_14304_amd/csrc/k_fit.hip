@@ -132,7 +132,7 @@ __global__ void sum_parts_kernel(const double *in, int stride, int n_in, int gro
 // K_m = sum_k a_{k nP + m} B_k (FP64), bg_m = a_{nb nP + m}: a workgroup per
 // 64 samples of a stamp, the basis values of 31 functions in flight (the sum
 // over k stays in order; with a workgroup per stamp and one load at a time
-// the launch took 27 us at 21 x 21, now 6 us)
+// the launch took 27 us at 21 x 21, now 5 us)
 __global__ __launch_bounds__(64) void expand_kernel(const BasisTables *T, const double *coeffs,
                                                     int n, int nP, int nPb, int K, int nb,
                                                     float *stamps, float *bg) {
@@ -297,7 +297,7 @@ int launch_fit(argus_ctx *ctx, argus_dims d, const argus_kernel_spec *spec, cons
     // every chunk's partial moments are written and read again (at about 3 TB/s
     // together).  Take the chunk count, chunks of 4 rows and up, with the
     // smallest sum: large frames get a last round that leaves few CUs idle,
-    // small ones many short chunks (256 x 224, degree 1: 94 -> 30 us against
+    // small ones many short chunks (256 x 224, degree 1: 94 -> 27 us against
     // chunks no shorter than 8h rows).
     {
         const int base = fa.RX * fa.RY * fa.spt;

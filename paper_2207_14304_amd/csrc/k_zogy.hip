@@ -25,8 +25,8 @@
 //   output   inverse rows, scaling, masks.
 // Two images in one transform share its rounding, so they are brought to one
 // scale by powers of two first: R by g = 2^k next to F_n / F_r (the images may
-// be in any units), S by the one next to 1 / sqrt(sum P_D^2) (the PSFs may have
-// any sums; their own transforms are kept apart).
+// be in any units), the reference's PSF by the one next to the ratio of the two
+// maxima, S by the one next to 1 / sqrt(sum P_D^2) (the PSFs may have any sums).
 // A length-L transform is L / 8 threads with 8 values each in registers and
 // radix-8 steps (one radix-4 or -2 step where 3 does not divide log2 L)
 // exchanged through LDS.  280 tiles of 512^2: 10.9 -> 1.69 ms, against two
