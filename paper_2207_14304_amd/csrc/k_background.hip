@@ -41,7 +41,9 @@ struct CellArgs {
 // their first digit, so there a wave adds its first lane's digit with one
 // atomic (64 lanes on one address take 64 turns); each thread clears the bins
 // it scans, so a digit takes three barriers.  Full frame, 64 x 64 cells: 267 ->
-// 122 us, against four 8-bit digits scanned by one wave.
+// 122 us, against four 8-bit digits scanned by one wave.  Cells of at most a pixel
+// a thread do one of a pass's 16 turns (1201x901, 4 x 4 cells: 414 us with four
+// digits, 441 with all turns, 371).
 __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
     constexpr int NB = 2048, PER = NB / NTHR;
     __shared__ __align__(16) int hist[NB];
@@ -58,6 +60,7 @@ __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
     // every load of a thread is issued before any is used
     float v[MAXV];
     uint8_t m[MAXV];
+    bool one = false;                      // at most one value a thread
     if (a.vec && (cw == 64 || cw == 32)) {
         const int lg = cw == 64 ? 4 : 3, row = tid >> lg, c4 = (tid & ((1 << lg) - 1)) * 4;
         const int step = NTHR >> lg;       // rows of a pass over the workgroup
@@ -80,6 +83,7 @@ __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
             }
         }
     } else {
+        one = np <= NTHR;
 #pragma unroll
         for (int k = 0; k < MAXV; ++k) {
             const int i = tid + k * NTHR;
@@ -107,6 +111,7 @@ __global__ __launch_bounds__(NTHR) void bg_cell_kernel(CellArgs a) {
         const uint32_t dmask = pass == 2 ? 1023u : 2047u;
 #pragma unroll
         for (int k = 0; k < MAXV; ++k) {
+            if (k == 1 && one) break;
             const bool ok = (okbits >> k) & 1u;
             const uint32_t d = (key[k] >> shift) & dmask;
             if (pass == 0) {

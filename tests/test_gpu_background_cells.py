@@ -27,3 +27,20 @@ def test_last_cell_of_a_word_width(W, box):
     o = bk.cell_levels(cal.astype(np.float64), mask, box).astype(np.float32)
     assert np.array_equal(host(lev), o)
     ctx.close()
+
+
+# cells of at most a pixel a thread (256), one more, and 256 pixels in words
+@pytest.mark.parametrize("W,H,box", [(61, 43, 4), (64, 48, 16), (68, 51, 17), (64, 40, 32)])
+def test_small_cells(W, H, box):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ctx = argus.Context(0)
+    rng = np.random.default_rng(box)
+    cal = rng.normal(800.0, 30.0, (H, W)).astype(np.float32)
+    mask = (rng.random((H, W)) < 0.1).astype(np.uint8)
+    lev, grid = (empty((-(-H // box), -(-W // box)), torch.float32) for _ in range(2))
+    ctx.background(dev(cal), dev(mask), box, grid, lev)
+    o = bk.cell_levels(cal.astype(np.float64), mask, box).astype(np.float32)
+    assert np.array_equal(host(lev), o, equal_nan=True)
+    ctx.close()
