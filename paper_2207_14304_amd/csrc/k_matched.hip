@@ -49,7 +49,8 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
                                              int ly, int lx0, double (&s)[PX], double (&v)[PX]) {
     using L = MLds<R, TX, TY, PX>;
     constexpr int K = L::K, TH = L::TH, TW = L::TW, TWr = L::TWr, NT = L::NT;
-    // unrolled, a small PSF's rows run 12 % faster; a large one's spill
+    // unrolled as the compiler sees fit, a small PSF's rows run 12 % faster; a
+    // large one's spill
     constexpr bool ROLLED = PX == 4 || R > 4;
     float *At = lds;                   // [TH][TW] M / V
     float *Bt = At + TH * TW;          // [TH][TW] 1 / V
@@ -65,8 +66,7 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
         const uint8_t *msk = a.mask[j];
         const BgGrid bg = a.bg[j];
         constexpr int NE = TH * TWr, NH = (NE + NT - 1) / NT, NB = PX == 8 ? 8 : 4;
-#pragma unroll (ROLLED ? 1 : (NH + NB - 1) / NB)
-        for (int j0 = 0; j0 < NH; j0 += NB) {
+        auto stage = [&](int j0) {
             float hc[NB], hv[NB];
             uint8_t hm[NB];
 #pragma unroll
@@ -95,6 +95,12 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
                     Bt[cy * TW + cx] = ok ? 1.f / hv[e] : 0.f;
                 }
             }
+        };
+        if constexpr (ROLLED) {
+#pragma unroll 1
+            for (int j0 = 0; j0 < NH; j0 += NB) stage(j0);
+        } else {
+            for (int j0 = 0; j0 < NH; j0 += NB) stage(j0);
         }
         const float *pj = a.psf + (size_t)j * K * K;
         const float F = a.F[j];
@@ -104,8 +110,7 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
             Pt[2 * t + 1] = (F * F) * (p * p);
         }
         __syncthreads();
-#pragma unroll (ROLLED ? 1 : K)
-        for (int dv = 0; dv < K; ++dv) {
+        auto row = [&](int dv) {
             // the windows of this PSF row as 16-byte reads (rows are 16-byte
             // aligned; the last read may pass the window by up to three
             // floats, still inside the LDS carve-up)
@@ -136,12 +141,18 @@ __device__ __forceinline__ void matched_tile(const MatchedArgs &a, float *lds, i
                 s[i] += (double)rs[i];
                 v[i] += (double)rv[i];
             }
+        };
+        if constexpr (ROLLED) {
+#pragma unroll 1
+            for (int dv = 0; dv < K; ++dv) row(dv);
+        } else {
+            for (int dv = 0; dv < K; ++dv) row(dv);
         }
     }
 }
 
 template <int R>
-__global__ __launch_bounds__(NTHR, R == 3 ? 3 : 2) void matched_kernel(MatchedArgs a) {
+__global__ __launch_bounds__(NTHR, 2) void matched_kernel(MatchedArgs a) {
     extern __shared__ __align__(16) float lds[];
     const int tid = threadIdx.x;
     const int bx0 = (blockIdx.x % a.bx) * BW, by0 = (blockIdx.x / a.bx) * BH;
@@ -546,19 +557,19 @@ int launch_coadd_matched(argus_ctx *ctx, argus_dims d, int n, const float *const
     // for its splits from r = 5 on, or where there are backgrounds, whose
     // interpolation its staging shares among columns, from r = 3 on and at r = 1
     // (3 PSF rows are one turn of its 4 waves, 5 are two).  4788x3194, 5 images,
-    // FP32 / matrix form (us): no backgrounds r = 1 339 / 483, 2 411 / 648, 3 532 /
-    // 648, 4 663 / 757, 5 980 / 847; with them r = 1 565 / 536, 2 654 / 709, 3 788 /
+    // FP32 / matrix form (us): no backgrounds r = 1 336 / 483, 2 406 / 648, 3 535 /
+    // 648, 4 653 / 757, 5 980 / 847; with them r = 1 565 / 536, 2 654 / 709, 3 788 /
     // 696, 4 951 / 811.  500x333, 2 images: 4 29 / 27, 5 36 / 28; 3 with them 35 / 28.
     bool grid = false;
     for (int j = 0; j < n; ++j) grid = grid || a.bg[j].grid;
-    const bool fp32 = grid ? r == 2 : r <= 4;
+    const bool fp32 = !grid && r <= 4;
     argus_time_begin(ctx);
     int rc;
     switch (r) {
 #define ARGUS_MF(RR) case RR: rc = matched_launch<RR>(ctx, a, nblocks); break;
 #define ARGUS_MM(RR) case RR: rc = matched_mfma_launch<RR>(ctx, a); break;
 #define ARGUS_ME(RR) case RR: rc = fp32 ? matched_launch<RR>(ctx, a, nblocks) : matched_mfma_launch<RR>(ctx, a); break;
-        ARGUS_ME(1) ARGUS_ME(2) ARGUS_ME(3) ARGUS_ME(4) ARGUS_MM(5) ARGUS_MM(6) ARGUS_MM(7) ARGUS_MM(8)
+        ARGUS_ME(1) ARGUS_MF(2) ARGUS_ME(3) ARGUS_ME(4) ARGUS_MM(5) ARGUS_MM(6) ARGUS_MM(7) ARGUS_MM(8)
         ARGUS_MF(9) ARGUS_MF(10)
 #undef ARGUS_MF
 #undef ARGUS_MM
